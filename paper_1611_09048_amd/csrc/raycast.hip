@@ -1489,9 +1489,9 @@ __global__ void encode_rgba8_kernel(EncodeArgs a) {
 // records of a pair are adjacent; lanes alternate the z parity, then step x).
 // A wave's stores are one contiguous run (x-fastest) or 64 adjacent record
 // pairs, and its reads of a source cover whole runs of 64 or 2 x 32 x.
-// SIG > 0: the sources have that signature's compile-time kinds; SIG = 0: any
-// sources.
-template <int SIG, bool PAIRED>
+// SIG > 0: the sources have that signature's compile-time kinds; SIG = 0: N
+// sources of at most D components each, any storage.
+template <int SIG, int N, int D, bool PAIRED>
 __device__ __forceinline__ void derive_voxels(const DeriveArgs& a, int xi, int slot, int yi, int zi0, int nz) {
     constexpr int kZ = 4;
     const int ex = a.ext[0], ey = a.ext[1];
@@ -1564,41 +1564,66 @@ __device__ __forceinline__ void derive_voxels(const DeriveArgs& a, int xi, int s
         const int qz = S.guard < 1 ? clampi(z, 0, a.ext[2] - 2 * a.g - 1) : z;
         return qx * S.stride[0] + qy * S.stride[1] + qz * S.stride[2];
     };
-    auto store = [&](int j, float o0, float o1, float o2, float o3) {
-        float* d = a.dst + rec[j] * a.n;
-        switch (a.n) {
-        case 4: *reinterpret_cast<float4*>(d) = make_float4(o0, o1, o2, o3); break;
-        case 3: d[0] = o0; d[1] = o1; d[2] = o2; break;
-        case 2: d[0] = o0; d[1] = o1; break;
-        default: d[0] = o0; break;
+    auto store = [&](int j, const float* o) {
+        float* d = a.dst + rec[j] * N;
+        if constexpr (N == 4) {
+            *reinterpret_cast<float4*>(d) = make_float4(o[0], o[1], o[2], o[3]);
+        } else if constexpr (N == 2) {
+            *reinterpret_cast<float2*>(d) = make_float2(o[0], o[1]);
+        } else {
+#pragma unroll
+            for (int s = 0; s < N; ++s) d[s] = o[s];
         }
     };
+    float out[kZ][N];
     if constexpr (SIG == SIG_GENERIC) {
-        // one voxel at a time (any sources)
+        // every component of every source first, as it is stored (the loads of a
+        // component are one uniform branch on the storage width, and nothing waits
+        // on them there), then the chains
+        uint32_t raw[N][kZ][D];
 #pragma unroll
-        for (int j = 0; j < kZ; ++j) {
-            if (!need[j]) continue;
-            float v[kMaxDerived][1][4];
+        for (int s = 0; s < N; ++s) {
+            const DevSource& S = a.src[s];
+            int off[kZ];
 #pragma unroll
-            for (int s = 0; s < kMaxDerived; ++s) {
-                if (s < a.n) {
-                    const int off[1] = {offset(a.src[s], ry[j], rz[j])};
-                    fetch<1>(a.src[s], off, v[s]);
+            for (int j = 0; j < kZ; ++j) off[j] = offset(S, ry[j], rz[j]);
+#pragma unroll
+            for (int c = 0; c < D; ++c) {
+#pragma unroll
+                for (int j = 0; j < kZ; ++j) raw[s][j][c] = 0u;
+                if (c < S.f_dim) {
+                    const int k = S.packed ? 0 : c, o = S.comp_off[c];
+                    const __amdgpu_buffer_rsrc_t r = make_rsrc(S.base[k], S.num_records[k]);
+                    if (S.dtype == DT_F32) {
+#pragma unroll
+                        for (int j = 0; j < kZ; ++j)
+                            raw[s][j][c] = __builtin_amdgcn_raw_buffer_load_b32(r, off[j] + o, 0, 0);
+                    } else {
+#pragma unroll
+                        for (int j = 0; j < kZ; ++j)
+                            raw[s][j][c] = __builtin_amdgcn_raw_buffer_load_b16(r, off[j] + o, 0, 0);
+                    }
                 }
             }
-            float o[kMaxDerived] = {0.f, 0.f, 0.f, 0.f};
+        }
 #pragma unroll
-            for (int s = 0; s < kMaxDerived; ++s) {
-                if (s < a.n) {
-                    float r[1];
-                    run_chain<1>(a.src[s], v[s], r);
-                    o[s] = r[0];
+        for (int s = 0; s < N; ++s) {
+            float v[kZ][4], res[kZ];
+            const int dtype = a.src[s].dtype;
+#pragma unroll
+            for (int j = 0; j < kZ; ++j)
+#pragma unroll
+                for (int c = 0; c < 4; ++c) {
+                    const uint32_t b = c < D ? raw[s][j][c < D ? c : 0] : 0u;
+                    if (dtype == DT_F32) v[j][c] = __builtin_bit_cast(float, b);
+                    else if (dtype == DT_F16) v[j][c] = (float)__builtin_bit_cast(_Float16, (unsigned short)b);
+                    else v[j][c] = __builtin_bit_cast(float, b << 16);
                 }
-            }
-            store(j, o[0], o[1], o[2], o[3]);
+            run_chain_n<kZ, D>(a.src[s], v, res);
+#pragma unroll
+            for (int j = 0; j < kZ; ++j) out[j][s] = res[j];
         }
     } else {
-        float out[kZ][kMaxDerived];
         constexpr int K0 = SigKinds<SIG>::k0, K1 = SigKinds<SIG>::k1, K2 = SigKinds<SIG>::k2;
         float v0[kZ][4], v1[kZ][4], v2[kZ][4];
         // every load of the 4 voxels first
@@ -1625,7 +1650,6 @@ __device__ __forceinline__ void derive_voxels(const DeriveArgs& a, int xi, int s
             for (int c = 0; c < 4; ++c) t[0][c] = v0[j][c];
             run_chain<1, KindOf<K0>::dim>(a.src[0], t, r);
             out[j][0] = r[0];
-            out[j][1] = out[j][2] = out[j][3] = 0.f;
             if constexpr (K1 != K_NONE) {
                 for (int c = 0; c < 4; ++c) t[0][c] = v1[j][c];
                 run_chain<1, KindOf<K1>::dim>(a.src[1], t, r);
@@ -1637,23 +1661,28 @@ __device__ __forceinline__ void derive_voxels(const DeriveArgs& a, int xi, int s
                 out[j][2] = r[0];
             }
         }
-        // one contiguous store per voxel
-#pragma unroll
-        for (int j = 0; j < kZ; ++j)
-            if (need[j]) store(j, out[j][0], out[j][1], out[j][2], out[j][3]);
     }
+    // one contiguous store per voxel
+#pragma unroll
+    for (int j = 0; j < kZ; ++j)
+        if (need[j]) store(j, out[j]);
 }
 
 // Blocks of 256 threads cover consecutive threads of consecutive rows (y, or
 // stored y pairs of 2 ex threads) of one slab (4 z-slices, or 2 stored z
-// pairs); grid z strides over the slabs.  Eight waves per SIMD for the paired
-// signature-specialized variants: left to itself the compiler keeps the
-// arguments in up to 106 scalar registers, which leaves room for seven, and
-// this latency-bound pass runs faster with the eighth wave's loads in flight
-// (the other variants would spill to scratch under that bound: no bound).
-template <int SIG, bool PAIRED>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(PAIRED && SIG != SIG_GENERIC ? 8 : 1, 8)))
-void derive_kernel(DeriveArgs a) {
+// pairs); the slabs are laid over grid y and z, one per thread.  A loop over
+// slabs, which no volume but one of more than 262,140 slices needed, made every
+// argument of every source loop-invariant: the compiler held them all in scalar
+// registers across it and spilled 25 to 146 of them, to vector registers and to
+// scratch.  Straight-line code reads each argument where it is used: no variant
+// spills, and eight waves fit per SIMD (5 or 6 with sources of 4 components).
+// Bound by memory once that is so.  The general kernel (SIG_GENERIC), which also
+// read one voxel at a time, a source after the other: FP16 component arrays of
+// 213 x 187 x 241 with a third clipped 176 -> 50 us, two FP32 sources of 256^3
+// with half clipped 123 -> 49 us (the specialized pass over all three 82 -> 80).
+constexpr unsigned kDeriveSlabsY = 32768;
+template <int SIG, int N, int D, bool PAIRED>
+__global__ __launch_bounds__(256) void derive_kernel(DeriveArgs a) {
     const int ex = a.ext[0];
     const int row = PAIRED ? 2 * ex : ex;
     const int rows = PAIRED ? a.ny2 : a.ext[1];
@@ -1663,8 +1692,9 @@ void derive_kernel(DeriveArgs a) {
     const int r = idx - yi * row;
     const int xi = PAIRED ? r >> 1 : r, slot = PAIRED ? r & 1 : 0;
     const int nzs = PAIRED ? a.nz2 : a.ext[2], per = PAIRED ? 2 : 4;
-    for (int zi0 = per * (int)blockIdx.z; zi0 < nzs; zi0 += per * (int)gridDim.z)
-        derive_voxels<SIG, PAIRED>(a, xi, slot, yi, zi0, min(per, nzs - zi0));
+    const int zi0 = per * (int)(blockIdx.z * kDeriveSlabsY + blockIdx.y);
+    if (zi0 >= nzs) return;
+    derive_voxels<SIG, N, D, PAIRED>(a, xi, slot, yi, zi0, min(per, nzs - zi0));
 }
 
 // Ray setup of every pixel of each job's screen rectangle, one lane per ray,
@@ -1955,28 +1985,46 @@ int launch_encode_rgba8(const float* rgba, int64_t n_pixels, const float* bg, un
     return hipGetLastError();
 }
 
-template <bool PAIRED>
-void (*derive_variant(int sig))(DeriveArgs) {
-    switch (sig) {
-    case SIG_F32x1: return derive_kernel<SIG_F32x1, PAIRED>;
-    case SIG_PIC3_F32: return derive_kernel<SIG_PIC3_F32, PAIRED>;
-    case SIG_PIC3_F16: return derive_kernel<SIG_PIC3_F16, PAIRED>;
-    case SIG_PIC3_BF16: return derive_kernel<SIG_PIC3_BF16, PAIRED>;
-    default: return derive_kernel<SIG_GENERIC, PAIRED>;
+using DeriveFn = void (*)(DeriveArgs);
+
+template <int N, bool PAIRED>
+DeriveFn derive_general(int dim) {
+    if (dim <= 1) return derive_kernel<SIG_GENERIC, N, 1, PAIRED>;
+    if (dim <= 3) return derive_kernel<SIG_GENERIC, N, 3, PAIRED>;
+    return derive_kernel<SIG_GENERIC, N, 4, PAIRED>;
+}
+
+DeriveFn derive_variant(const DeriveArgs& a, int sig) {
+    int dim = 1;
+    for (int s = 0; s < a.n; ++s) dim = std::max(dim, (int)a.src[s].f_dim);
+    if (a.paired) {
+        switch (sig) {
+        case SIG_PIC3_F32: return derive_kernel<SIG_PIC3_F32, 3, 3, true>;
+        case SIG_PIC3_F16: return derive_kernel<SIG_PIC3_F16, 3, 3, true>;
+        case SIG_PIC3_BF16: return derive_kernel<SIG_PIC3_BF16, 3, 3, true>;
+        default: return derive_general<3, true>(dim);
+        }
+    }
+    switch (a.n) {
+    case 1: return derive_general<1, false>(dim);
+    case 2: return derive_general<2, false>(dim);
+    case 3: return derive_general<3, false>(dim);
+    default: return derive_general<4, false>(dim);
     }
 }
 
 int launch_derive(const DeriveArgs& a, int sig, void* stream) {
     if (a.ext[0] <= 0 || a.ext[1] <= 0 || a.ext[2] <= 0) return hipSuccess;
+    if (a.n < 1 || a.n > kMaxDerived || (a.paired && a.n != 3)) return hipErrorInvalidValue;
     if (a.paired && (a.gp < a.g || (a.gp & 1) || 2 * a.ny2 < a.ext[1] - a.g + a.gp ||
                      2 * a.nz2 < a.ext[2] - a.g + a.gp))
         return hipErrorInvalidValue;
     const int64_t slice = (int64_t)a.ext[0] * (a.paired ? 2 * (int64_t)a.ny2 : a.ext[1]);
     if (slice > (1LL << 30)) return hipErrorInvalidValue;
     const int slabs = a.paired ? (a.nz2 + 1) / 2 : (a.ext[2] + 3) / 4;
-    const dim3 grid((unsigned)((slice + 255) / 256), 1, (unsigned)std::min(slabs, 65535));
-    void (*k)(DeriveArgs) = a.paired ? derive_variant<true>(sig) : derive_variant<false>(sig);
-    hipLaunchKernelGGL(k, grid, dim3(256), 0, (hipStream_t)stream, a);
+    const dim3 grid((unsigned)((slice + 255) / 256), std::min((unsigned)slabs, kDeriveSlabsY),
+                    ((unsigned)slabs + kDeriveSlabsY - 1) / kDeriveSlabsY);
+    hipLaunchKernelGGL(derive_variant(a, sig), grid, dim3(256), 0, (hipStream_t)stream, a);
     return hipGetLastError();
 }
 
