@@ -377,24 +377,36 @@ bool finite3(const double v[3]) { return std::isfinite(v[0]) && std::isfinite(v[
 
 // Which compile-time specialized loop (if any) fits the job's active sources.
 int32_t signature_of(const DevJob& dj) {
-    if (dj.n_src == 3) {
-        // the three sources of one derived volume (either layout), in order
-        const DevSource* d = dj.src;
+    const DevSource* d0 = dj.src;
+    auto small = [](const DevSource& d) {
+        bool ok = true;
+        for (int a = 0; a < 3; ++a) ok = ok && std::abs((int64_t)d.stride[a]) < (1 << 23);
+        return ok;
+    };
+    if (dj.n_src >= 2 && dj.n_src <= 4) {
+        // the two, three (either layout) or four sources of one derived volume, in order
         bool il = true;
-        for (int s = 0; s < 3; ++s)
-            il = il && d[s].f_dim == 1 && d[s].dtype == DT_F32 && d[s].n_ops == 0 && d[s].base[0] == d[0].base[0] &&
-                 d[s].num_records[0] == d[0].num_records[0] && d[s].comp_off[0] == d[0].comp_off[0] + 4 * s &&
-                 d[s].guard >= 1 && d[s].layout == d[0].layout && d[s].stride[0] == (d[s].layout ? 48 : 12) &&
-                 d[s].stride[1] == d[0].stride[1] && d[s].stride[2] == d[0].stride[2] && d[s].stride[1] < (1 << 23) &&
-                 d[s].stride[2] < (1 << 23);
-        if (il) return d[0].layout ? SIG_IL3P : SIG_IL3;
+        for (int s = 0; s < dj.n_src; ++s) {
+            const DevSource& d = d0[s];
+            il = il && d.f_dim == 1 && d.dtype == DT_F32 && d.n_ops == 0 && d.base[0] == d0->base[0] &&
+                 d.num_records[0] == d0->num_records[0] && d.comp_off[0] == d0->comp_off[0] + 4 * s && d.guard >= 1 &&
+                 d.layout == d0->layout && d.stride[0] == (d.layout ? 48 : 4 * dj.n_src) &&
+                 d.stride[1] == d0->stride[1] && d.stride[2] == d0->stride[2] && d.stride[1] >= 0 &&
+                 d.stride[2] >= 0 && small(d);
+        }
+        if (il && dj.n_src == 3) return d0->layout ? SIG_IL3P : SIG_IL3;
+        if (il && d0->layout == 0) return dj.n_src == 2 ? SIG_IL2 : SIG_IL4;
+    }
+    // one plain scalar whose x neighbours are adjacent (any y and z strides): x pairs in one load
+    if (dj.n_src == 1 && d0->packed && d0->layout == 0 && d0->f_dim == 1 && d0->dtype == DT_F32 && d0->n_ops == 0 &&
+        d0->stride[0] == 4 && small(*d0)) {
+        if (d0->guard >= 1 || !dj.interp) return SIG_IL1;
+        if (dj.dims[0] >= 2) return SIG_IL1C;
     }
     int kinds[kMaxSources];
     for (int s = 0; s < dj.n_src; ++s) {
         const DevSource& d = dj.src[s];
-        bool small = true;
-        for (int a = 0; a < 3; ++a) small = small && std::abs((int64_t)d.stride[a]) < (1 << 23);
-        if (!d.packed || !small || (d.f_dim != 1 && d.f_dim != 3)) return SIG_GENERIC;
+        if (!d.packed || !small(d) || (d.f_dim != 1 && d.f_dim != 3)) return SIG_GENERIC;
         if (dj.n_src == 3 && d.guard < 1) return SIG_GENERIC;   // the three-source loops assume guard layers
         kinds[s] = d.dtype * 2 + (d.f_dim == 3 ? 1 : 0);   // dtype-major: F32x1=0, F32x3=1, F16x1=2, ...
     }
@@ -695,9 +707,15 @@ isaac_status enqueue_jobs(isaac_context* ctx, const isaac_render_desc* jobs, con
     la.lanes = lanes;
     la.waves_hint = (lanes == 2 || lanes >= 32 || unroll > 1) ? 0 : hint;
     la.sig = djs[0].sig;
+    auto scalar = [](int sig) { return sig == SIG_F32x1 || sig == SIG_IL1 || sig == SIG_IL1C; };
+    bool scalars = true;
+    for (const DevJob& dj : djs) scalars = scalars && scalar(dj.sig);
     for (const DevJob& dj : djs)
-        if (dj.sig != la.sig) la.sig = -1;
-    if (la.sig == SIG_GENERIC) la.sig = -1;
+        if (dj.sig != la.sig) la.sig = scalars ? (int)SIG_F32x1 : -1;
+    // FP32 scalars of different forms in one launch: the loop that takes any of them
+    // (the dispatching kernel keeps 3 waves per SIMD, that loop 8)
+    if (scalars && la.sig == SIG_F32x1)
+        for (int i = 0; i < n; ++i) r->host[i].sig = SIG_F32x1;
     la.mode = djs[0].mode;
     if (la.mode == ISAAC_ISO) {
         // the plain-source iso kernel when every source is a packed FP32 scalar without
@@ -873,11 +891,12 @@ isaac_status derive_volumes(isaac_context* ctx, const isaac_render_desc* jobs, s
         int comp_of[kMaxSources];
         for (int s = 0; s < kMaxSources; ++s) comp_of[s] = -1;
         double est = 0.0;
-        bool benefit = false;
+        bool benefit = false, clamps = false;
         int g = 0;
         for (int i = 0; i < n; ++i) {
             if (jobs[i].volume_id != vid) continue;
             const DevJob& dj = djs[i];
+            clamps = clamps || (dj.interp && dj.mode != ISAAC_ISO);
             est += estimate_samples(dj) * (dj.interp ? 8.0 : 1.0);
             for (int k = 0; k < dj.n_src; ++k) {
                 const DevSource& d = dj.src[k];
@@ -890,6 +909,13 @@ isaac_status derive_volumes(isaac_context* ctx, const isaac_render_desc* jobs, s
         for (int s = 0; s < kMaxSources; ++s)
             if (comp_of[s] >= 0) comp_of[s] = nd++;
         if (nd == 0 || nd > kMaxDerived || !benefit) continue;
+        if (!force && est < 4.0 * (double)(v.dims[0] + 2 * g) * (v.dims[1] + 2 * g) * (v.dims[2] + 2 * g)) continue;
+        // trilinear volume jobs over sources without guard layers: a derived guard layer
+        // that repeats the border values makes the loop's border clamp unnecessary (where
+        // it fits the size limit below; + 3: the pairs' rounding)
+        if (g == 0 && clamps &&
+            16.0 * (v.dims[0] + 3.0) * (v.dims[1] + 3.0) * (v.dims[2] + 3.0) < (double)((int64_t)1 << 31))
+            g = 1;
         const int64_t ex = v.dims[0] + 2 * g, ey = v.dims[1] + 2 * g, ez = v.dims[2] + 2 * g;
         // The derived sources in either layout: x fastest, or (three sources) the (y, z)
         // pairs, stored y and z shifted by gp, an even number of layers at least g, so
@@ -922,7 +948,9 @@ isaac_status derive_volumes(isaac_context* ctx, const isaac_render_desc* jobs, s
         auto describe = [&](DevJob& dj, const Layout& L, void* base) {
             for (int k = 0; k < dj.n_src; ++k) {
                 DevSource& d = dj.src[k];
-                const int guard = d.guard;
+                // guard cells hold the border values where a source has none; the iso
+                // loops reach farther than one layer and keep the source's own rule
+                const int guard = dj.mode == ISAAC_ISO ? d.guard : std::max((int)d.guard, g > 0 ? 1 : 0);
                 std::memset(d.base, 0, sizeof d.base);
                 std::memset(d.num_records, 0, sizeof d.num_records);
                 std::memset(d.comp_off, 0, sizeof d.comp_off);
@@ -956,7 +984,6 @@ isaac_status derive_volumes(isaac_context* ctx, const isaac_render_desc* jobs, s
         const Layout L = layout_of(paired);
         const size_t bytes = L.bytes;
         if (bytes >= ((size_t)1 << 31)) continue;
-        if (!force && est < 4.0 * (double)(ex * ey * ez)) continue;
         if (v.derived_bytes != bytes) {
             if (v.derived) {
                 HIP_TRY(ctx, hipStreamSynchronize(stream));
@@ -1023,7 +1050,7 @@ isaac_status derive_volumes(isaac_context* ctx, const isaac_render_desc* jobs, s
         probe.n_src = nd;
         for (int k = 0; k < nd; ++k) probe.src[k] = da.src[k];
         const int dsig = signature_of(probe);
-        int rc = launch_derive(da, dsig == SIG_IL3 || dsig == SIG_IL3P ? (int)SIG_GENERIC : dsig, stream);
+        int rc = launch_derive(da, dsig, stream);
         if (rc != hipSuccess) return set_err(ctx, ISAAC_ERR_DEVICE, "derive launch: %s", hipGetErrorString((hipError_t)rc));
         for (int i = 0; i < n; ++i) {
             if (jobs[i].volume_id != vid) continue;
@@ -1100,6 +1127,7 @@ isaac_status render_impl(isaac_context* ctx, const isaac_render_desc* jobs, int 
             d.f_dim = 1;
             d.dtype = DT_F32;
             d.n_ops = 0;
+            if (t.mode != ISAAC_ISO) d.guard = f.guard;
         }
         if (t.mode != ISAAC_ISO) t.sig = signature_of(t);
         const bool paired = t.n_src > 0 && t.src[0].layout == 1;

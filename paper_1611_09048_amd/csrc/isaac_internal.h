@@ -56,6 +56,10 @@ enum Signature : int32_t {
     SIG_PIC3_BF16 = 4,    // the same in BF16
     SIG_IL3 = 5,          // a three-source derived volume, x fastest (DevSource layout 0)
     SIG_IL3P = 6,         // a three-source derived volume in (y, z) pairs (DevSource layout 1)
+    SIG_IL1 = 7,          // one plain FP32 scalar (no functors, x neighbours adjacent), in place or derived
+    SIG_IL1C = 8,         // the same without guard layers, trilinear (border clamp)
+    SIG_IL2 = 9,          // a two-source derived volume, x fastest
+    SIG_IL4 = 10,         // a four-source derived volume, x fastest
 };
 
 struct DevSource {

@@ -520,59 +520,115 @@ __device__ __forceinline__ void fetch_kind(const DevSource& S, const int (&off)[
     }
 }
 
-// The 8 trilinear corners (or the nearest cell) of a three-source derived
-// volume, 12-byte records, same corner order as corner_offsets.
-// PAIRED (layout 1, (y, z) pairs): the x + 1 corners are 48 bytes on (the
+// The signatures whose sources are plain FP32 values side by side: n values
+// per voxel, in (y, z) pairs or x fastest, with or without a border clamp.
+template <int SIG> struct Il { static constexpr int n = 0; static constexpr bool paired = false, clamp = false; };
+template <> struct Il<SIG_IL1> { static constexpr int n = 1; static constexpr bool paired = false, clamp = false; };
+template <> struct Il<SIG_IL1C> { static constexpr int n = 1; static constexpr bool paired = false, clamp = true; };
+template <> struct Il<SIG_IL2> { static constexpr int n = 2; static constexpr bool paired = false, clamp = false; };
+template <> struct Il<SIG_IL3> { static constexpr int n = 3; static constexpr bool paired = false, clamp = false; };
+template <> struct Il<SIG_IL3P> { static constexpr int n = 3; static constexpr bool paired = true, clamp = false; };
+template <> struct Il<SIG_IL4> { static constexpr int n = 4; static constexpr bool paired = false, clamp = false; };
+
+// The 8 trilinear corners (or the nearest cell) of such a volume, same corner
+// order as corner_offsets.  A gather costs the texture-address unit one cycle
+// per cache line its 64 lanes touch (at least 16 for more than 4 bytes a lane),
+// whatever its width, so a load takes as many corners as are adjacent:
+// one and two sources (4 and 8 bytes a voxel): both x corners in one load, 4
+// loads instead of 8 (a batch of 64 FP32 scalars 1.88 -> 1.17 ms, bound by the
+// address unit before) or, two derived sources, instead of 16 by the general
+// loop (192 x 160 x 224 with a third clipped at 1280 x 720: 142 -> 47 us);
+// three, x fastest, and four: one load per corner;
+// three, PAIRED (layout 1, (y, z) pairs): the x + 1 corners are 48 bytes on (the
 // loads' scalar offset); the y + 1 and z + 1 corners lie in the same pair or
 // the next one depending on the parity of the index.  A wave's gathers of one
 // corner touch fewer cache lines on oblique rays than in the x-fastest layout.
-// Layout 0 (x fastest): two per-lane base offsets (z0 and z1 planes) and the
-// wave-uniform x/y corner steps in the scalar offset.
-template <int INTERP, bool PAIRED>
-__device__ __forceinline__ void fetch_il3(const DevSource& S, const int (&i0)[3], float (&v)[INTERP ? 8 : 1][4]) {
+// A derived volume's y and z steps travel in the loads' scalar offset (its
+// strides are not negative); a scalar read in place may have any strides, and
+// its whole offset is subject to the buffer's range check.
+template <int INTERP, int SIG>
+__device__ __forceinline__ void fetch_il(const DevSource& S, const int dims[3], const int (&i0)[3],
+                                         float (&v)[INTERP ? 8 : 1][4]) {
+    typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
+    typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+    constexpr int N = Il<SIG>::n;
+    static_assert(!(Il<SIG>::paired && Il<SIG>::clamp), "derived pairs have guard layers");
     const __amdgpu_buffer_rsrc_t r = make_rsrc(S.base[0], S.num_records[0]);
     const int sx = __builtin_amdgcn_readfirstlane(S.stride[0]);
     const int sy = __builtin_amdgcn_readfirstlane(S.stride[1]);
     const int sz = __builtin_amdgcn_readfirstlane(S.stride[2]);
-    auto ld3 = [&](int vo, int so, float (&d)[4]) {
-        d[0] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(r, vo, so, 0));
-        d[1] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(r, vo + 4, so, 0));
-        d[2] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(r, vo + 8, so, 0));
-        d[3] = 0.f;
+    auto f32 = [](unsigned b) { return __builtin_bit_cast(float, b); };
+    // one voxel
+    auto ld = [&](int vo, int so, float (&d)[4]) {
+        if constexpr (N == 4) {
+            const u32x4 b = __builtin_amdgcn_raw_buffer_load_b128(r, vo, so, 0);
+            d[0] = f32(b.x), d[1] = f32(b.y), d[2] = f32(b.z), d[3] = f32(b.w);
+        } else {
+            d[0] = f32(__builtin_amdgcn_raw_buffer_load_b32(r, vo, so, 0));
+            if constexpr (N > 1) d[1] = f32(__builtin_amdgcn_raw_buffer_load_b32(r, vo + 4, so, 0));
+            if constexpr (N > 2) d[2] = f32(__builtin_amdgcn_raw_buffer_load_b32(r, vo + 8, so, 0));
+        }
     };
-    if constexpr (PAIRED) {
+    // voxels x and x + 1 (adjacent)
+    auto ld_pair = [&](int vo, int so, float (&d0)[4], float (&d1)[4]) {
+        if constexpr (N == 1) {
+            const u32x2 b = __builtin_amdgcn_raw_buffer_load_b64(r, vo, so, 0);
+            d0[0] = f32(b.x), d1[0] = f32(b.y);
+        } else if constexpr (N == 2) {
+            const u32x4 b = __builtin_amdgcn_raw_buffer_load_b128(r, vo, so, 0);
+            d0[0] = f32(b.x), d0[1] = f32(b.y), d1[0] = f32(b.z), d1[1] = f32(b.w);
+        } else {
+            ld(vo, so, d0);
+            ld(vo, so + sx, d1);
+        }
+    };
+    if constexpr (Il<SIG>::paired) {
         const int yl = i0[1] & 1, zl = i0[2] & 1;
         const int b0 = __mul24(i0[2] >> 1, sz) + __mul24(i0[1] >> 1, sy) + __mul24(i0[0], sx) + __mul24(zl, 24) +
                        __mul24(yl, 12) + S.comp_off[0];
         if constexpr (INTERP == 0) {
-            ld3(b0, 0, v[0]);
+            ld(b0, 0, v[0]);
         } else {
             const int oy = __mul24(yl, sy - 24) + 12;   // y + 1: same pair (+12) or the next one
             const int oz = __mul24(zl, sz - 48) + 24;   // z + 1: same pair (+24) or the next one
             const int b2 = b0 + oy, b4 = b0 + oz, b6 = b4 + oy;
-            ld3(b0, 0, v[0]);
-            ld3(b0, sx, v[1]);
-            ld3(b2, 0, v[2]);
-            ld3(b2, sx, v[3]);
-            ld3(b4, 0, v[4]);
-            ld3(b4, sx, v[5]);
-            ld3(b6, 0, v[6]);
-            ld3(b6, sx, v[7]);
+            ld_pair(b0, 0, v[0], v[1]);
+            ld_pair(b2, 0, v[2], v[3]);
+            ld_pair(b4, 0, v[4], v[5]);
+            ld_pair(b6, 0, v[6], v[7]);
+        }
+    } else if constexpr (Il<SIG>::clamp && INTERP != 0) {
+        // the x pair from the last place it fits; at a border both corners are the border voxel
+        const int xb = clampi(i0[0], 0, dims[0] - 2);
+        const int bx = __mul24(xb, sx) + S.comp_off[0];
+        const int y0 = __mul24(clampi(i0[1], 0, dims[1] - 1), sy), y1 = __mul24(clampi(i0[1] + 1, 0, dims[1] - 1), sy);
+        const int z0 = __mul24(clampi(i0[2], 0, dims[2] - 1), sz), z1 = __mul24(clampi(i0[2] + 1, 0, dims[2] - 1), sz);
+        ld_pair(bx + y0 + z0, 0, v[0], v[1]);
+        ld_pair(bx + y1 + z0, 0, v[2], v[3]);
+        ld_pair(bx + y0 + z1, 0, v[4], v[5]);
+        ld_pair(bx + y1 + z1, 0, v[6], v[7]);
+#pragma unroll
+        for (int i = 0; i < 8; i += 2) {
+            const float lo = v[i][0], hi = v[i + 1][0];
+            v[i][0] = i0[0] > xb ? hi : lo;
+            v[i + 1][0] = i0[0] < xb ? lo : hi;
         }
     } else {
         const int b0 = __mul24(i0[0], sx) + __mul24(i0[1], sy) + __mul24(i0[2], sz) + S.comp_off[0];
         if constexpr (INTERP == 0) {
-            ld3(b0, 0, v[0]);
+            ld(b0, 0, v[0]);
+        } else if constexpr (N == 1) {
+            const int b1 = b0 + sz;
+            ld_pair(b0, 0, v[0], v[1]);
+            ld_pair(b0 + sy, 0, v[2], v[3]);
+            ld_pair(b1, 0, v[4], v[5]);
+            ld_pair(b1 + sy, 0, v[6], v[7]);
         } else {
             const int b1 = b0 + sz;
-            ld3(b0, 0, v[0]);
-            ld3(b0, sx, v[1]);
-            ld3(b0, sy, v[2]);
-            ld3(b0, sx + sy, v[3]);
-            ld3(b1, 0, v[4]);
-            ld3(b1, sx, v[5]);
-            ld3(b1, sy, v[6]);
-            ld3(b1, sx + sy, v[7]);
+            ld_pair(b0, 0, v[0], v[1]);
+            ld_pair(b0, sy, v[2], v[3]);
+            ld_pair(b1, 0, v[4], v[5]);
+            ld_pair(b1, sy, v[6], v[7]);
         }
     }
 }
@@ -637,8 +693,6 @@ template <> struct SigKinds<SIG_F32x1> { static constexpr int k0 = K_F32x1, k1 =
 template <> struct SigKinds<SIG_PIC3_F32> { static constexpr int k0 = K_F32x1, k1 = K_F32x3, k2 = K_F32x3; };
 template <> struct SigKinds<SIG_PIC3_F16> { static constexpr int k0 = K_F16x1, k1 = K_F16x3, k2 = K_F16x3; };
 template <> struct SigKinds<SIG_PIC3_BF16> { static constexpr int k0 = K_BF16x1, k1 = K_BF16x3, k2 = K_BF16x3; };
-template <> struct SigKinds<SIG_IL3> { static constexpr int k0 = K_F32x1, k1 = K_F32x1, k2 = K_F32x1; };
-template <> struct SigKinds<SIG_IL3P> { static constexpr int k0 = K_F32x1, k1 = K_F32x1, k2 = K_F32x1; };
 
 // PS (per source): load, chain, blend and classify one source before the
 // next one's loads; fewer live registers (more resident waves) at the cost of
@@ -688,14 +742,14 @@ __device__ __forceinline__ void points(const DevJob& J, const float4* __restrict
             E[u][1] = fmaf(wa, cl.y, E[u][1]);
             E[u][2] = fmaf(wa, cl.z, E[u][2]);
         };
-        if constexpr (SIG == SIG_IL3 || SIG == SIG_IL3P) {
-            // the three chain outputs of a voxel are adjacent: one 12-byte load per corner
+        if constexpr (Il<SIG>::n > 0) {
+            // the values of a voxel are adjacent
 #pragma unroll
             for (int u = 0; u < U; ++u) {
                 float v[NV][4];
-                fetch_il3<INTERP, SIG == SIG_IL3P>(J.src[0], i0[u], v);
+                fetch_il<INTERP, SIG>(J.src[0], dims, i0[u], v);
 #pragma unroll
-                for (int s = 0; s < 3; ++s) {
+                for (int s = 0; s < Il<SIG>::n; ++s) {
                     float c[NV];
 #pragma unroll
                     for (int i = 0; i < NV; ++i) c[i] = v[i][s];
@@ -890,13 +944,13 @@ __device__ __forceinline__ bool lanes_row(const DevJob& J, const float4* __restr
     return row_composite<G>(J, R, lane, k0, valid, E[0][0], E[0][1], E[0][2], S[0], acc);
 }
 
-// Interleaved derived volume (SIG_IL3), G lanes per ray, software-pipelined:
+// Plain values side by side (Il<SIG>), G lanes per ray, software-pipelined:
 // the corner loads of a lane's next scan point are issued before the current
 // one is blended, classified and composited, so a row's memory latency
 // overlaps the previous row's arithmetic.  The arithmetic is that of
 // lanes_row, operation for operation.
 template <int INTERP>
-__device__ __forceinline__ void il3_locate(const DevJob& J, const RaySetup& R, int k, int (&i0)[3], float (&w)[3]) {
+__device__ __forceinline__ void il_locate(const DevJob& J, const RaySetup& R, int k, int (&i0)[3], float (&w)[3]) {
     const int kk = min(k, R.ke - 1);
     float p[3];
     if (INTERP == 0) point_at(J, R, ((float)kk + 0.5f) * (float)J.step, p);
@@ -914,13 +968,13 @@ __device__ __forceinline__ void il3_locate(const DevJob& J, const RaySetup& R, i
     }
 }
 
-template <int NV>
-__device__ __forceinline__ void il3_mix(const DevJob& J, const float4* __restrict__ s_tf, const float (&v)[NV][4],
+template <int NV, int N>
+__device__ __forceinline__ void il_mix(const DevJob& J, const float4* __restrict__ s_tf, const float (&v)[NV][4],
                                         const float (&w)[3], float (&E)[3], float& S) {
     S = 0.f;
     E[0] = E[1] = E[2] = 0.f;
 #pragma unroll
-    for (int s = 0; s < 3; ++s) {
+    for (int s = 0; s < N; ++s) {
         float c[NV];
 #pragma unroll
         for (int i = 0; i < NV; ++i) c[i] = v[i][s];
@@ -934,31 +988,32 @@ __device__ __forceinline__ void il3_mix(const DevJob& J, const float4* __restric
     mix_finish(S, E);
 }
 
-template <int INTERP, int G, bool PAIRED>
-__device__ __forceinline__ void march_lanes_il3(const DevJob& J, const float4* __restrict__ s_tf, const RaySetup& R,
-                                                int lane, float4& out, int& count) {
+template <int INTERP, int G, int SIG>
+__device__ __forceinline__ void march_lanes_il(const DevJob& J, const float4* __restrict__ s_tf, const RaySetup& R,
+                                               int lane, float4& out, int& count) {
     constexpr int NV = INTERP ? 8 : 1;
+    const int dims[3] = {J.dims[0], J.dims[1], J.dims[2]};
     const int g = lane & (G - 1);
     int i0[3];
     float w[3], v[NV][4];
-    il3_locate<INTERP>(J, R, R.kb + g, i0, w);
-    fetch_il3<INTERP, PAIRED>(J.src[0], i0, v);
+    il_locate<INTERP>(J, R, R.kb + g, i0, w);
+    fetch_il<INTERP, SIG>(J.src[0], dims, i0, v);
     RayAccum acc = {0.f, 0.f, 0.f, 0.f, 0};
     for (int k0 = R.kb;; k0 += G) {
         // the next row's loads (clamped to the last scan point: always in bounds)
         int i0n[3];
         float wn[3], vn[NV][4];
-        il3_locate<INTERP>(J, R, k0 + G + g, i0n, wn);
-        fetch_il3<INTERP, PAIRED>(J.src[0], i0n, vn);
+        il_locate<INTERP>(J, R, k0 + G + g, i0n, wn);
+        fetch_il<INTERP, SIG>(J.src[0], dims, i0n, vn);
         const bool valid = k0 + g < R.ke;
         float E[3], S;
-        il3_mix<NV>(J, s_tf, v, w, E, S);
+        il_mix<NV, Il<SIG>::n>(J, s_tf, v, w, E, S);
         if (row_composite<G>(J, R, lane, k0, valid, E[0], E[1], E[2], S, acc))
             break;
 #pragma unroll
         for (int i = 0; i < NV; ++i)
 #pragma unroll
-            for (int c = 0; c < 4; ++c) v[i][c] = vn[i][c];
+            for (int c = 0; c < Il<SIG>::n; ++c) v[i][c] = vn[i][c];
         w[0] = wn[0];
         w[1] = wn[1];
         w[2] = wn[2];
@@ -987,8 +1042,7 @@ template <int INTERP, int U, int G, int SIG, bool PS>
 __device__ __forceinline__ void march_sig(const DevJob& J, const float4* __restrict__ s_tf, const RaySetup& R,
                                           int lane, float4& out, int& count) {
     if constexpr (G == 1) march_seq<INTERP, (SIG == SIG_GENERIC ? 1 : U), SIG, PS>(J, s_tf, R, out, count);
-    else if constexpr ((SIG == SIG_IL3 || SIG == SIG_IL3P) && !PS)
-        march_lanes_il3<INTERP, G, SIG == SIG_IL3P>(J, s_tf, R, lane, out, count);
+    else if constexpr (Il<SIG>::n > 0 && !PS) march_lanes_il<INTERP, G, SIG>(J, s_tf, R, lane, out, count);
     else march_lanes<INTERP, G, SIG, PS>(J, s_tf, R, lane, out, count);
 }
 
@@ -1002,6 +1056,10 @@ __device__ __forceinline__ void march_dispatch(const DevJob& J, const float4* __
     case SIG_PIC3_BF16: march_sig<INTERP, U, G, SIG_PIC3_BF16, PS>(J, s_tf, R, lane, out, count); break;
     case SIG_IL3: march_sig<INTERP, U, G, SIG_IL3, PS>(J, s_tf, R, lane, out, count); break;
     case SIG_IL3P: march_sig<INTERP, U, G, SIG_IL3P, PS>(J, s_tf, R, lane, out, count); break;
+    case SIG_IL1: march_sig<INTERP, U, G, SIG_IL1, PS>(J, s_tf, R, lane, out, count); break;
+    case SIG_IL1C: march_sig<INTERP, U, G, SIG_IL1C, PS>(J, s_tf, R, lane, out, count); break;
+    case SIG_IL2: march_sig<INTERP, U, G, SIG_IL2, PS>(J, s_tf, R, lane, out, count); break;
+    case SIG_IL4: march_sig<INTERP, U, G, SIG_IL4, PS>(J, s_tf, R, lane, out, count); break;
     default: march_sig<INTERP, U, G, SIG_GENERIC, PS>(J, s_tf, R, lane, out, count); break;
     }
 }
@@ -1308,6 +1366,10 @@ __device__ __forceinline__ bool pool_row(const DevJob& J, const float4* __restri
         case SIG_PIC3_BF16: return lanes_row<INTERP, G, SIG_PIC3_BF16, PS>(J, s_tf, R, lane, k0, acc);
         case SIG_IL3: return lanes_row<INTERP, G, SIG_IL3, PS>(J, s_tf, R, lane, k0, acc);
         case SIG_IL3P: return lanes_row<INTERP, G, SIG_IL3P, PS>(J, s_tf, R, lane, k0, acc);
+        case SIG_IL1: return lanes_row<INTERP, G, SIG_IL1, PS>(J, s_tf, R, lane, k0, acc);
+        case SIG_IL1C: return lanes_row<INTERP, G, SIG_IL1C, PS>(J, s_tf, R, lane, k0, acc);
+        case SIG_IL2: return lanes_row<INTERP, G, SIG_IL2, PS>(J, s_tf, R, lane, k0, acc);
+        case SIG_IL4: return lanes_row<INTERP, G, SIG_IL4, PS>(J, s_tf, R, lane, k0, acc);
         default: return lanes_row<INTERP, G, SIG_GENERIC, PS>(J, s_tf, R, lane, k0, acc);
         }
     }
@@ -1838,10 +1900,15 @@ KernelFn pick_kernel(int mode, int sig, int unroll, int lanes, int hint) {
     case SIG_PIC3_BF16: return pick_specialized<SIG_PIC3_BF16>(unroll, lanes, hint);
     case SIG_IL3: return pick_specialized<SIG_IL3>(unroll, lanes, hint);
     case SIG_IL3P: return pick_specialized<SIG_IL3P>(unroll, lanes, hint);
+    case SIG_IL1: return pick_specialized<SIG_IL1>(unroll, lanes, hint);
+    case SIG_IL1C: return pick_specialized<SIG_IL1C>(unroll, lanes, hint);
+    case SIG_IL2: return pick_specialized<SIG_IL2>(unroll, lanes, hint);
+    case SIG_IL4: return pick_specialized<SIG_IL4>(unroll, lanes, hint);
+    case SIG_GENERIC: return pick_specialized<SIG_GENERIC>(unroll, lanes, 1);
     default:
         break;
     }
-    // mixed or generic signatures: the dispatching kernels (one lane-count each)
+    // mixed signatures: the dispatching kernels (one lane-count each)
     switch (lanes) {
     case 64: return raycast_kernel<1, 64, 0, -1>;
     case 32: return raycast_kernel<1, 32, 0, -1>;
@@ -1902,6 +1969,8 @@ PoolFn pick_pool_kernel(int sig, int lanes, int hint) {
     case SIG_PIC3_BF16: return pick_pool_specialized<SIG_PIC3_BF16>(lanes, hint);
     case SIG_IL3: return pick_pool_specialized<SIG_IL3>(lanes, hint);
     case SIG_IL3P: return pick_pool_specialized<SIG_IL3P>(lanes, hint);
+    case SIG_GENERIC: return pick_pool_specialized<SIG_GENERIC>(lanes, hint);
+    case SIG_IL1: return pick_pool_specialized<SIG_IL1>(lanes, hint);
     default: break;
     }
     switch (lanes) {
