@@ -336,8 +336,8 @@ isaac_status isaac_timing(isaac_context* ctx, double* total_ms, int* count);
  *   wave_w, a power of two in [1, 64/lanes_per_ray]: a wave's rays form a
  *     wave_w x (64/lanes_per_ray/wave_w) pixel block;
  *   waves_x in {1,2,4}: the 4 waves of a workgroup are waves_x x 4/waves_x;
- *   unroll in {1,2} (one lane per ray only): scan points whose source reads
- *     are issued together;
+ *   unroll in {1,2} (one lane per ray only): 2 asks for two scan points' reads
+ *     together; both settings now run the schedule below;
  *   min_waves in {0,4}: 4 selects the kernel variant compiled to keep at
  *     least 4 waves resident per SIMD (not with lanes_per_ray 2, 32, 64 or
  *     unroll 2);
@@ -349,10 +349,12 @@ isaac_status isaac_timing(isaac_context* ctx, double* total_ms, int* count);
  *     kept in the context); serving and batched launches use the tiles.
  * A batch runs one launch per distinct schedule, so each job is rendered as
  * it would be alone.
- * Defaults: (8, 2, 1, 1, 0, 0).  Settings with one lane per ray give the same
- * image bit for bit; more lanes composite each row of scan points by a scan,
- * which changes only FP32 rounding; a given setting always reproduces its
- * image bit for bit. */
+ * Defaults: (8, 2, 1, 1, 0, 0).  One lane per ray fixes the arithmetic, a ray's
+ * points composited one after another; the points are evaluated by groups of 4
+ * or 16 lanes, whichever suits the number of rays (a wave then holds 16 or 4 of
+ * them).  Settings with one lane per ray give the same image bit for bit; more
+ * lanes composite each row of scan points by a scan, which changes only FP32
+ * rounding; a given setting always reproduces its image bit for bit. */
 isaac_status isaac_set_tile_shape(isaac_context* ctx, int size_class, int wave_w, int waves_x, int unroll,
                                   int lanes_per_ray, int min_waves, int pooled);
 isaac_status isaac_get_tile_shape(isaac_context* ctx, int size_class, int* wave_w, int* waves_x, int* unroll,

@@ -38,6 +38,13 @@ using isaac::host::set_cull_rect;
 namespace {
 
 constexpr int kRingSlots = 16;
+// Jobs of one lane per ray: the rays of a launch from which groups of 4 lanes
+// evaluate them instead of 16.  Few rays need 16 to fill the chip; many are as fast
+// or faster with 4, whose in-order compositing takes a quarter of the instructions
+// per point.  Measured, us a call for 4 and 16 lanes: 36 K rays (512^2, one scalar) 47
+// and 38; 92 K (720p, three derived sources) 74 and 77, (four) 139 and 129; 217 K
+// (1080p, three) 236 and 234; 867 K (4K, three) 405 and 466.
+constexpr size_t kOrderedWideRays = 1 << 18;
 constexpr int kTfSlots = 4096;      // transfer tables resident at once (16 MiB)
 
 struct Status {
@@ -96,7 +103,7 @@ struct RingSlot {
     // graph cache
     hipGraphExec_t exec = nullptr;
     hipGraph_t graph = nullptr;
-    int g_jobs = -1, g_tiles = -1, g_grid = -1, g_src = -1, g_unroll = -1, g_lanes = -1, g_hint = -1, g_sig = -3;
+    int g_jobs = -1, g_tiles = -1, g_grid = -1, g_src = -1, g_ordered = -1, g_lanes = -1, g_hint = -1, g_sig = -3;
     unsigned g_fill = 0;
     int g_dense = -1;
 };
@@ -422,9 +429,8 @@ int32_t signature_of(const DevJob& dj) {
 // Tile decomposition of a job for a launch running `lanes` lanes per ray.
 // Tiles cover only the job's screen rectangle (cull); the pixels outside it
 // are cleared by a fill kernel.
-void set_tiles(DevJob& dj, int lanes, int unroll) {
+void set_tiles(DevJob& dj, int lanes) {
     dj.lanes = lanes;
-    dj.unroll = lanes > 1 ? 1 : unroll;
     const int rays = 64 / lanes;
     if (dj.wave_w > rays) dj.wave_w = rays;
     const int tw = dj.wave_w * dj.waves_x, th = (rays / dj.wave_w) * (4 / dj.waves_x);
@@ -536,11 +542,10 @@ isaac_status build_job(isaac_context* ctx, const isaac_render_desc& j, bool need
     const TileShape& ts = ctx->shapes[size_class_of(j.width, j.height)];
     dj.wave_w = ts.wave_w;
     dj.waves_x = ts.waves_x;
-    dj.unroll = ts.unroll;
     dj.lanes = ts.lanes;
     dj.waves_hint = ts.waves_hint;
     dj.pool = ts.pool;
-    set_tiles(dj, ts.lanes, ts.unroll);
+    set_tiles(dj, ts.lanes);
     dj.out = j.out_rgba;
     dj.out_samples = j.out_samples;
     int n_act = 0;
@@ -583,12 +588,12 @@ isaac_status build_job(isaac_context* ctx, const isaac_render_desc& j, bool need
     dj.mode = j.mode;
     dj.sig = signature_of(dj);
     if (dj.mode == ISAAC_ISO) {
-        // iso jobs run their own kernel with the runtime source loop: 8 lanes per
-        // ray when the size class asks for several, else one
+        // iso jobs run their own kernel with the runtime source loop, 8 lanes per
+        // ray (the image is that of one lane, bit for bit)
         dj.sig = SIG_GENERIC;
         dj.waves_hint = 0;
         dj.pool = 0;
-        set_tiles(dj, ts.lanes >= 8 ? 8 : 1, 1);
+        set_tiles(dj, 8);
     }
     *n_active_out = n_act;
     return ISAAC_OK;
@@ -675,17 +680,19 @@ isaac_status enqueue_jobs(isaac_context* ctx, const isaac_render_desc* jobs, con
     RingSlot* r = nullptr;
     isaac_status st = acquire_slot(ctx, &r);
     if (st) return st;
-    // one kernel variant per launch: the most lanes per ray any job asks for,
-    // else the deepest unroll; every job's tiles follow the launch's variant
-    int lanes = 1, unroll = 1, hint = 0;
-    for (const DevJob& dj : djs) lanes = std::max(lanes, (int)dj.lanes);
-    for (const DevJob& dj : djs) hint = std::max(hint, (int)dj.waves_hint);
-    if (lanes == 1)
-        for (const DevJob& dj : djs) unroll = std::max(unroll, (int)dj.unroll);
+    // one kernel variant per launch (the caller groups jobs by schedule)
+    int lanes = djs[0].lanes, hint = djs[0].waves_hint;
+    const bool ordered = lanes == 1;
+    if (ordered) {
+        size_t rays = 0;
+        for (const DevJob& dj : djs)
+            rays += (size_t)std::max(0, dj.cull[2] - dj.cull[0] + 1) * std::max(0, dj.cull[3] - dj.cull[1] + 1);
+        lanes = rays < kOrderedWideRays ? 16 : 4;
+    }
     int tiles = 0;
     for (int i = 0; i < n; ++i) {
         r->host[i] = djs[i];
-        set_tiles(r->host[i], lanes, unroll);
+        set_tiles(r->host[i], lanes);
         r->host[i].tile_begin = tiles;
         tiles += r->host[i].tiles_x * r->host[i].tiles_y;
     }
@@ -703,9 +710,9 @@ isaac_status enqueue_jobs(isaac_context* ctx, const isaac_render_desc* jobs, con
     la.persistent = n > 1 ? 1 : 0;
     la.grid = std::max(1, ctx->n_cu * ctx->blocks_per_cu);
     la.max_src = std::max(1, max_src);
-    la.unroll = unroll;
+    la.ordered = ordered ? 1 : 0;
     la.lanes = lanes;
-    la.waves_hint = (lanes == 2 || lanes >= 32 || unroll > 1) ? 0 : hint;
+    la.waves_hint = hint;
     la.sig = djs[0].sig;
     auto scalar = [](int sig) { return sig == SIG_F32x1 || sig == SIG_IL1 || sig == SIG_IL1C; };
     bool scalars = true;
@@ -774,7 +781,7 @@ isaac_status enqueue_jobs(isaac_context* ctx, const isaac_render_desc* jobs, con
     const bool use_graph = n > 1 && !(flags & ISAAC_NO_GRAPH) && !noalloc;
     if (use_graph) {
         if (!r->exec || r->g_jobs != n || r->g_tiles != tiles || r->g_grid != la.grid || r->g_src != la.max_src ||
-            r->g_unroll != la.unroll || r->g_lanes != la.lanes || r->g_hint != la.waves_hint || r->g_sig != la.sig ||
+            r->g_ordered != la.ordered || r->g_lanes != la.lanes || r->g_hint != la.waves_hint || r->g_sig != la.sig ||
             r->g_fill != la.fill_blocks || r->g_dense != la.dense_setup) {
             if (r->exec) hipGraphExecDestroy(r->exec);
             if (r->graph) hipGraphDestroy(r->graph);
@@ -798,7 +805,7 @@ isaac_status enqueue_jobs(isaac_context* ctx, const isaac_render_desc* jobs, con
             r->g_tiles = tiles;
             r->g_grid = la.grid;
             r->g_src = la.max_src;
-            r->g_unroll = la.unroll;
+            r->g_ordered = la.ordered;
             r->g_lanes = la.lanes;
             r->g_hint = la.waves_hint;
             r->g_sig = la.sig;
@@ -808,7 +815,7 @@ isaac_status enqueue_jobs(isaac_context* ctx, const isaac_render_desc* jobs, con
         if (t0) HIP_TRY(ctx, hipEventRecord(t0, stream));
         HIP_TRY(ctx, hipGraphLaunch(r->exec, stream));
         if (t1) HIP_TRY(ctx, hipEventRecord(t1, stream));
-    } else if (n == 1 && allow_pool && !noalloc && djs[0].pool && lanes >= 2 && lanes <= 16 &&
+    } else if (n == 1 && allow_pool && !noalloc && djs[0].pool && !ordered && lanes <= 16 &&
                djs[0].mode == ISAAC_VOLUME &&
                (size_t)djs[0].width * djs[0].height * ray_record_bytes() < ((size_t)1 << 31) &&
                ensure_pool(ctx, (size_t)djs[0].width * djs[0].height * ray_record_bytes(), stream)) {
@@ -1138,11 +1145,11 @@ isaac_status render_impl(isaac_context* ctx, const isaac_render_desc* jobs, int 
         if (st) return st;
     }
     // one launch per scan-point schedule, so every job is rendered exactly as
-    // it would be alone (its size class's lanes per ray, unroll and variant)
+    // it would be alone (its size class's lanes per ray and variant)
     std::vector<std::vector<DevJob>> groups;
     std::vector<int> keys;
     for (const DevJob& dj : djs) {
-        const int key = dj.mode * 2048 + dj.pool * 1024 + dj.lanes * 16 + dj.unroll * 2 + dj.waves_hint;
+        const int key = dj.mode * 2048 + dj.pool * 1024 + dj.lanes * 2 + (dj.lanes > 1 ? dj.waves_hint : 0);
         size_t g = 0;
         while (g < keys.size() && keys[g] != key) ++g;
         if (g == keys.size()) {

@@ -110,8 +110,7 @@ struct DevJob {
     // tile decomposition of this job's image
     int32_t wave_w;        // a wave's rays form a wave_w x (64 / lanes / wave_w) block
     int32_t waves_x;       // waves per workgroup: waves_x x (4 / waves_x)
-    int32_t unroll;        // scan points whose loads are issued together (1 or 2)
-    int32_t lanes;         // lanes sharing one ray (1, 2, 4, 8 or 16)
+    int32_t lanes;         // lanes sharing one ray (1: composited as by one lane, evaluated by several)
     int32_t waves_hint;    // 1: run the variant compiled for at least 4 waves per SIMD
     int32_t sig;           // Signature of the active sources
     int32_t mode;          // 0 volume compositing, 1 first iso-surface
@@ -137,8 +136,8 @@ struct LaunchArgs {
     int persistent;            // 0: one workgroup per tile; 1: grid-stride over a tile queue
     int grid;                  // workgroups launched in persistent mode
     int max_src;               // widest job's active source count (sizes the LDS tables)
-    int unroll;                // scan points whose loads are issued together (kernel variant)
-    int lanes;                 // lanes per ray (kernel variant); 1 when unroll > 1
+    int ordered;               // 1: jobs of one lane per ray, evaluated by groups of `lanes` (4 or 16) lanes
+    int lanes;                 // lanes per ray (kernel variant)
     int waves_hint;            // 1: the variant compiled for at least 4 waves per SIMD
     int sig;                   // the jobs' common Signature, or -1 when they differ
     int mode;                  // 1: iso-surface jobs (all jobs of a launch share the mode)

@@ -1,7 +1,7 @@
 // Volume ray casting kernels for gfx950 (MI355X).
 //
-// One ray per lane; a 64-lane wave covers a wave_w x (64/wave_w) pixel
-// block and a 256-thread workgroup a 2-D arrangement of four such blocks.
+// G lanes per ray; a 64-lane wave covers a block of wave_w x (64/G/wave_w)
+// pixels and a 256-thread workgroup a 2-D arrangement of four such blocks.
 // For every pixel the kernel builds the ray in FP64, intersects it with the
 // local box and the clipping planes (the kept scan points along a ray form
 // one interval of the sample index k), then marches in FP32: at each scan
@@ -647,11 +647,10 @@ __device__ __forceinline__ float blend(const float (&c)[N], const float (&w)[3])
 
 // ---------------------------------------------------------------------------
 // Scan points.  point_generic evaluates one scan point with the runtime
-// source loop (any sources); points<...> evaluates U consecutive scan points
-// for a compile-time source signature, issuing every load before any is
-// consumed (the source loop unrolled at compile time, as the paper does with
-// template metaprogramming, Sec. 3.2).  Both return the mixed premultiplied
-// colour E and opacity S of each point and round alike at every step (the
+// source loop (any sources); point<...> for a compile-time source signature,
+// issuing every load before any is consumed (the source loop unrolled at
+// compile time, as the paper does with template metaprogramming, Sec. 3.2).
+// Both return the mixed premultiplied colour E and opacity S of the point and round alike at every step (the
 // trilinear cell coordinates come from point_at and a subtraction of 1/2 in
 // one, from cell_at in the other, which give the same numbers), so they give
 // the same image bit for bit.
@@ -688,6 +687,25 @@ __device__ __forceinline__ void point_generic(const DevJob& J, const float4* __r
     mix_finish(S, E);
 }
 
+// Cell indices and interpolation weights of scan point k (nearest: the clamped cell).
+template <int INTERP>
+__device__ __forceinline__ void locate(const DevJob& J, const RaySetup& R, int k, int (&i0)[3], float (&w)[3]) {
+    float p[3];
+    if (INTERP == 0) point_at(J, R, ((float)k + 0.5f) * (float)J.step, p);
+    else cell_at(J, R, k, p);
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+        if (INTERP == 0) {
+            i0[a] = clampi((int)floorf(p[a]), 0, J.dims[a] - 1);
+            w[a] = 0.f;
+        } else {
+            const float fl = floorf(p[a]);
+            w[a] = p[a] - fl;
+            i0[a] = (int)fl;
+        }
+    }
+}
+
 template <int SIG> struct SigKinds { static constexpr int k0 = K_NONE, k1 = K_NONE, k2 = K_NONE; };
 template <> struct SigKinds<SIG_F32x1> { static constexpr int k0 = K_F32x1, k1 = K_NONE, k2 = K_NONE; };
 template <> struct SigKinds<SIG_PIC3_F32> { static constexpr int k0 = K_F32x1, k1 = K_F32x3, k2 = K_F32x3; };
@@ -697,12 +715,11 @@ template <> struct SigKinds<SIG_PIC3_BF16> { static constexpr int k0 = K_BF16x1,
 // PS (per source): load, chain, blend and classify one source before the
 // next one's loads; fewer live registers (more resident waves) at the cost of
 // one memory round trip per source.  Same arithmetic either way.
-template <int INTERP, int U, int SIG, bool PS>
-__device__ __forceinline__ void points(const DevJob& J, const float4* __restrict__ s_tf, const RaySetup& R, int k,
-                                       float (&E)[U][3], float (&S)[U]) {
+template <int INTERP, int SIG, bool PS>
+__device__ __forceinline__ void point(const DevJob& J, const float4* __restrict__ s_tf, const RaySetup& R, int k,
+                                      float (&E)[3], float& S) {
     if constexpr (SIG == SIG_GENERIC) {
-        static_assert(U == 1, "the generic loop evaluates one scan point at a time");
-        point_generic<INTERP>(J, s_tf, R, k, E[0], S[0]);
+        point_generic<INTERP>(J, s_tf, R, k, E, S);
     } else {
         constexpr int K0 = SigKinds<SIG>::k0, K1 = SigKinds<SIG>::k1, K2 = SigKinds<SIG>::k2;
         constexpr int KS[3] = {K0, K1, K2};
@@ -710,131 +727,157 @@ __device__ __forceinline__ void points(const DevJob& J, const float4* __restrict
         constexpr int NS = (K0 != K_NONE) + (K1 != K_NONE) + (K2 != K_NONE);
         // the host admits the three-source signatures only with guard layers: no border clamp
         constexpr bool CL = SIG == SIG_F32x1;
-        const float step = (float)J.step;
         const int dims[3] = {J.dims[0], J.dims[1], J.dims[2]};
-        int i0[U][3];
-        float wts[U][3];
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int kk = min(k + u, R.ke - 1);
-            float p[3];
-            if (INTERP == 0) point_at(J, R, ((float)kk + 0.5f) * step, p);
-            else cell_at(J, R, kk, p);
-#pragma unroll
-            for (int a = 0; a < 3; ++a) {
-                if (INTERP == 0) {
-                    i0[u][a] = clampi((int)floorf(p[a]), 0, dims[a] - 1);
-                    wts[u][a] = 0.f;
-                } else {
-                    const float fl = floorf(p[a]);
-                    wts[u][a] = p[a] - fl;
-                    i0[u][a] = (int)fl;
-                }
-            }
-            S[u] = 0.f;
-            E[u][0] = E[u][1] = E[u][2] = 0.f;
-        }
-        auto accumulate = [&](int u, int s, float x) {
+        int i0[3];
+        float w[3];
+        locate<INTERP>(J, R, k, i0, w);
+        S = 0.f;
+        E[0] = E[1] = E[2] = 0.f;
+        auto accumulate = [&](int s, float x) {
             const float4 cl = classify(s_tf + s * kTfLds, x);
             const float wa = J.src[s].weight * cl.w;
-            S[u] = fmaf(J.src[s].weight, cl.w, S[u]);
-            E[u][0] = fmaf(wa, cl.x, E[u][0]);
-            E[u][1] = fmaf(wa, cl.y, E[u][1]);
-            E[u][2] = fmaf(wa, cl.z, E[u][2]);
+            S = fmaf(J.src[s].weight, cl.w, S);
+            E[0] = fmaf(wa, cl.x, E[0]);
+            E[1] = fmaf(wa, cl.y, E[1]);
+            E[2] = fmaf(wa, cl.z, E[2]);
         };
         if constexpr (Il<SIG>::n > 0) {
             // the values of a voxel are adjacent
+            float v[NV][4];
+            fetch_il<INTERP, SIG>(J.src[0], dims, i0, v);
 #pragma unroll
-            for (int u = 0; u < U; ++u) {
-                float v[NV][4];
-                fetch_il<INTERP, SIG>(J.src[0], dims, i0[u], v);
+            for (int s = 0; s < Il<SIG>::n; ++s) {
+                float c[NV];
 #pragma unroll
-                for (int s = 0; s < Il<SIG>::n; ++s) {
-                    float c[NV];
-#pragma unroll
-                    for (int i = 0; i < NV; ++i) c[i] = v[i][s];
-                    accumulate(u, s, blend<NV>(c, wts[u]));
-                }
+                for (int i = 0; i < NV; ++i) c[i] = v[i][s];
+                accumulate(s, blend<NV>(c, w));
             }
         } else if constexpr (PS) {
 #pragma unroll
             for (int s = 0; s < NS; ++s) {
-#pragma unroll
-                for (int u = 0; u < U; ++u) {
-                    int off[NV];
-                    float v[NV][4], c[NV];
-                    corner_offsets<INTERP, CL>(J.src[s], dims, i0[u], off);
-                    if (s == 0) fetch_kind<KS[0], NV>(J.src[0], off, v);
-                    else if (s == 1) fetch_kind<KS[1], NV>(J.src[1], off, v);
-                    else fetch_kind<KS[2], NV>(J.src[2], off, v);
-                    if (s == 0) run_chain<NV, KindOf<KS[0]>::dim>(J.src[0], v, c);
-                    else if (s == 1) run_chain<NV, KindOf<KS[1]>::dim>(J.src[1], v, c);
-                    else run_chain<NV, KindOf<KS[2]>::dim>(J.src[2], v, c);
-                    accumulate(u, s, blend<NV>(c, wts[u]));
-                }
+                int off[NV];
+                float v[NV][4], c[NV];
+                corner_offsets<INTERP, CL>(J.src[s], dims, i0, off);
+                if (s == 0) fetch_kind<KS[0], NV>(J.src[0], off, v);
+                else if (s == 1) fetch_kind<KS[1], NV>(J.src[1], off, v);
+                else fetch_kind<KS[2], NV>(J.src[2], off, v);
+                if (s == 0) run_chain<NV, KindOf<KS[0]>::dim>(J.src[0], v, c);
+                else if (s == 1) run_chain<NV, KindOf<KS[1]>::dim>(J.src[1], v, c);
+                else run_chain<NV, KindOf<KS[2]>::dim>(J.src[2], v, c);
+                accumulate(s, blend<NV>(c, w));
             }
         } else {
-            // every load of U scan points first, then chains, interpolation, classification
-            float vals[U][3][NV][4];
-#pragma unroll
-            for (int u = 0; u < U; ++u) {
-                int off[NV];
-                if (NS > 0) {
-                    corner_offsets<INTERP, CL>(J.src[0], dims, i0[u], off);
-                    fetch_kind<K0, NV>(J.src[0], off, vals[u][0]);
-                }
-                if (NS > 1) {
-                    corner_offsets<INTERP, CL>(J.src[1], dims, i0[u], off);
-                    fetch_kind<K1, NV>(J.src[1], off, vals[u][1]);
-                }
-                if (NS > 2) {
-                    corner_offsets<INTERP, CL>(J.src[2], dims, i0[u], off);
-                    fetch_kind<K2, NV>(J.src[2], off, vals[u][2]);
-                }
+            // every source's loads first, then chains, interpolation, classification
+            float vals[3][NV][4];
+            int off[NV];
+            if (NS > 0) {
+                corner_offsets<INTERP, CL>(J.src[0], dims, i0, off);
+                fetch_kind<K0, NV>(J.src[0], off, vals[0]);
+            }
+            if (NS > 1) {
+                corner_offsets<INTERP, CL>(J.src[1], dims, i0, off);
+                fetch_kind<K1, NV>(J.src[1], off, vals[1]);
+            }
+            if (NS > 2) {
+                corner_offsets<INTERP, CL>(J.src[2], dims, i0, off);
+                fetch_kind<K2, NV>(J.src[2], off, vals[2]);
             }
 #pragma unroll
-            for (int u = 0; u < U; ++u) {
-#pragma unroll
-                for (int s = 0; s < NS; ++s) {
-                    float c[NV];
-                    if (s == 0) run_chain<NV, KindOf<KS[0]>::dim>(J.src[0], vals[u][0], c);
-                    else if (s == 1) run_chain<NV, KindOf<KS[1]>::dim>(J.src[1], vals[u][1], c);
-                    else run_chain<NV, KindOf<KS[2]>::dim>(J.src[2], vals[u][2], c);
-                    accumulate(u, s, blend<NV>(c, wts[u]));
-                }
+            for (int s = 0; s < NS; ++s) {
+                float c[NV];
+                if (s == 0) run_chain<NV, KindOf<KS[0]>::dim>(J.src[0], vals[0], c);
+                else if (s == 1) run_chain<NV, KindOf<KS[1]>::dim>(J.src[1], vals[1], c);
+                else run_chain<NV, KindOf<KS[2]>::dim>(J.src[2], vals[2], c);
+                accumulate(s, blend<NV>(c, w));
             }
         }
-#pragma unroll
-        for (int u = 0; u < U; ++u) mix_finish(S[u], E[u]);
+        mix_finish(S, E);
     }
 }
 
-// One lane per ray: classical front-to-back compositing, U scan points per
-// step, early termination at the first point whose opacity reaches ert.
-template <int INTERP, int U, int SIG, bool PS>
-__device__ __forceinline__ void march_seq(const DevJob& J, const float4* __restrict__ s_tf, const RaySetup& R,
-                                          float4& out, int& count) {
-    const float ert = J.ert;
-    float Cr = 0.f, Cg = 0.f, Cb = 0.f, A = 0.f;
-    int n = 0;
-    bool done = false;
-    for (int k = R.kb; k < R.ke && !done; k += U) {
-        float E[U][3], S[U];
-        points<INTERP, U, SIG, PS>(J, s_tf, R, k, E, S);
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            if (k + u < R.ke && !done) {
-                const float T = 1.f - A;
-                Cr = fmaf(T, E[u][0], Cr);
-                Cg = fmaf(T, E[u][1], Cg);
-                Cb = fmaf(T, E[u][2], Cb);
-                A = fmaf(T, S[u], A);
-                ++n;
-                if (A >= ert) done = true;
-            }
-        }
+// A row of G points, one per lane of the group (G = 4: a quad, G = 16: a row of
+// lanes), composited in order onto (C0, C1, C2, A), on every lane of the group:
+// per point T = 1 - A and four fused multiply-adds that take the point's lane by
+// DPP (quad_perm, row_newbcast).  In assembly, 5 instructions per point: the
+// compiler does not fold a broadcast into fmac and issues 9.  The nop keeps the
+// wait states a DPP read needs after a write of its source or of EXEC; nothing
+// inside writes either.
+#define ISAAC_OVER(DPP)                                                              \
+    "v_sub_f32 %4, 1.0, %3\n\t"                                                      \
+    "v_fmac_f32_dpp %0, %5, %4 " DPP " row_mask:0xf bank_mask:0xf\n\t"               \
+    "v_fmac_f32_dpp %1, %6, %4 " DPP " row_mask:0xf bank_mask:0xf\n\t"               \
+    "v_fmac_f32_dpp %2, %7, %4 " DPP " row_mask:0xf bank_mask:0xf\n\t"               \
+    "v_fmac_f32_dpp %3, %8, %4 " DPP " row_mask:0xf bank_mask:0xf\n\t"
+template <int G>
+__device__ __forceinline__ void over_in_order(const float (&E)[3], float S, float& C0, float& C1, float& C2, float& A) {
+    static_assert(G == 4 || G == 16, "a quad or a row");
+    float t;
+    if constexpr (G == 4) {
+        asm("s_nop 4\n\t"
+            ISAAC_OVER("quad_perm:[0,0,0,0]") ISAAC_OVER("quad_perm:[1,1,1,1]")
+            ISAAC_OVER("quad_perm:[2,2,2,2]") ISAAC_OVER("quad_perm:[3,3,3,3]")
+            : "+&v"(C0), "+&v"(C1), "+&v"(C2), "+&v"(A), "=&v"(t)
+            : "v"(E[0]), "v"(E[1]), "v"(E[2]), "v"(S));
+    } else {
+        asm("s_nop 4\n\t"
+            ISAAC_OVER("row_newbcast:0") ISAAC_OVER("row_newbcast:1") ISAAC_OVER("row_newbcast:2")
+            ISAAC_OVER("row_newbcast:3") ISAAC_OVER("row_newbcast:4") ISAAC_OVER("row_newbcast:5")
+            ISAAC_OVER("row_newbcast:6") ISAAC_OVER("row_newbcast:7") ISAAC_OVER("row_newbcast:8")
+            ISAAC_OVER("row_newbcast:9") ISAAC_OVER("row_newbcast:10") ISAAC_OVER("row_newbcast:11")
+            ISAAC_OVER("row_newbcast:12") ISAAC_OVER("row_newbcast:13") ISAAC_OVER("row_newbcast:14")
+            ISAAC_OVER("row_newbcast:15")
+            : "+&v"(C0), "+&v"(C1), "+&v"(C2), "+&v"(A), "=&v"(t)
+            : "v"(E[0]), "v"(E[1]), "v"(E[2]), "v"(S));
     }
-    out = make_float4(Cr, Cg, Cb, A);
+}
+#undef ISAAC_OVER
+
+// One lane per ray as far as the image goes: the scan points of a ray are
+// composited one after another, front to back, with early termination at the
+// first whose opacity reaches ert.  They are evaluated by a group of G lanes, a
+// row of G points at a time (a lane alone on a ray waits for one gather after
+// another, and a frame's rays are too few to fill the chip with one lane each);
+// every lane of the group then composites the row in order, so the arithmetic,
+// and the image, are those of a single lane.  Opacities do not decrease along
+// a row, so a row whose last opacity is below ert holds no termination; the one
+// row of a ray that does is composited again point by point.  A point past the
+// ray's end has E = S = 0, which changes nothing.  Against a lane of its own per
+// ray, which waited on one gather after another (144 waves for 256^2 pixels): one
+// 64^3 scalar at 256^2 67 -> 23 us a call, three sources read in place at 512 x 300
+// 910 -> 88, four derived at 720p 689 -> 129, one scalar at 4K 1395 -> 503.
+template <int INTERP, int G, int SIG, bool PS>
+__device__ __forceinline__ void march_ordered(const DevJob& J, const float4* __restrict__ s_tf, const RaySetup& R,
+                                              int lane, float4& out, int& count) {
+    const int g = lane & (G - 1);
+    float C0 = 0.f, C1 = 0.f, C2 = 0.f, A = 0.f;
+    int n = 0;
+    for (int k0 = R.kb; k0 < R.ke; k0 += G) {
+        const int k = k0 + g;
+        const bool valid = k < R.ke;
+        float E[3], S;
+        point<INTERP, SIG, PS>(J, s_tf, R, valid ? k : R.ke - 1, E, S);
+        if (!valid) E[0] = E[1] = E[2] = S = 0.f;
+        float N0 = C0, N1 = C1, N2 = C2, NA = A;
+        over_in_order<G>(E, S, N0, N1, N2, NA);
+        if (NA >= J.ert) {
+            for (int j = 0; j < G; ++j) {
+                const float T = 1.f - A;
+                C0 = fmaf(__shfl(E[0], j, G), T, C0);
+                C1 = fmaf(__shfl(E[1], j, G), T, C1);
+                C2 = fmaf(__shfl(E[2], j, G), T, C2);
+                A = fmaf(__shfl(S, j, G), T, A);
+                ++n;
+                if (A >= J.ert) break;
+            }
+            break;
+        }
+        C0 = N0;
+        C1 = N1;
+        C2 = N2;
+        A = NA;
+        n += min(G, R.ke - k0);
+    }
+    out = make_float4(C0, C1, C2, A);
     count = n;
 }
 
@@ -939,9 +982,9 @@ __device__ __forceinline__ bool lanes_row(const DevJob& J, const float4* __restr
     const int g = lane & (G - 1);
     const int k = k0 + g;
     const bool valid = k < R.ke;
-    float E[1][3], S[1];
-    points<INTERP, 1, SIG, PS>(J, s_tf, R, valid ? k : R.ke - 1, E, S);
-    return row_composite<G>(J, R, lane, k0, valid, E[0][0], E[0][1], E[0][2], S[0], acc);
+    float E[3], S;
+    point<INTERP, SIG, PS>(J, s_tf, R, valid ? k : R.ke - 1, E, S);
+    return row_composite<G>(J, R, lane, k0, valid, E[0], E[1], E[2], S, acc);
 }
 
 // Plain values side by side (Il<SIG>), G lanes per ray, software-pipelined:
@@ -949,25 +992,6 @@ __device__ __forceinline__ bool lanes_row(const DevJob& J, const float4* __restr
 // one is blended, classified and composited, so a row's memory latency
 // overlaps the previous row's arithmetic.  The arithmetic is that of
 // lanes_row, operation for operation.
-template <int INTERP>
-__device__ __forceinline__ void il_locate(const DevJob& J, const RaySetup& R, int k, int (&i0)[3], float (&w)[3]) {
-    const int kk = min(k, R.ke - 1);
-    float p[3];
-    if (INTERP == 0) point_at(J, R, ((float)kk + 0.5f) * (float)J.step, p);
-    else cell_at(J, R, kk, p);
-#pragma unroll
-    for (int a = 0; a < 3; ++a) {
-        if (INTERP == 0) {
-            i0[a] = clampi((int)floorf(p[a]), 0, J.dims[a] - 1);
-            w[a] = 0.f;
-        } else {
-            const float fl = floorf(p[a]);
-            w[a] = p[a] - fl;
-            i0[a] = (int)fl;
-        }
-    }
-}
-
 template <int NV, int N>
 __device__ __forceinline__ void il_mix(const DevJob& J, const float4* __restrict__ s_tf, const float (&v)[NV][4],
                                         const float (&w)[3], float (&E)[3], float& S) {
@@ -996,14 +1020,14 @@ __device__ __forceinline__ void march_lanes_il(const DevJob& J, const float4* __
     const int g = lane & (G - 1);
     int i0[3];
     float w[3], v[NV][4];
-    il_locate<INTERP>(J, R, R.kb + g, i0, w);
+    locate<INTERP>(J, R, min(R.kb + g, R.ke - 1), i0, w);
     fetch_il<INTERP, SIG>(J.src[0], dims, i0, v);
     RayAccum acc = {0.f, 0.f, 0.f, 0.f, 0};
     for (int k0 = R.kb;; k0 += G) {
         // the next row's loads (clamped to the last scan point: always in bounds)
         int i0n[3];
         float wn[3], vn[NV][4];
-        il_locate<INTERP>(J, R, k0 + G + g, i0n, wn);
+        locate<INTERP>(J, R, min(k0 + G + g, R.ke - 1), i0n, wn);
         fetch_il<INTERP, SIG>(J.src[0], dims, i0n, vn);
         const bool valid = k0 + g < R.ke;
         float E[3], S;
@@ -1038,29 +1062,29 @@ __device__ __forceinline__ void march_lanes(const DevJob& J, const float4* __res
     count = acc.n;
 }
 
-template <int INTERP, int U, int G, int SIG, bool PS>
+template <int INTERP, bool ORD, int G, int SIG, bool PS>
 __device__ __forceinline__ void march_sig(const DevJob& J, const float4* __restrict__ s_tf, const RaySetup& R,
                                           int lane, float4& out, int& count) {
-    if constexpr (G == 1) march_seq<INTERP, (SIG == SIG_GENERIC ? 1 : U), SIG, PS>(J, s_tf, R, out, count);
+    if constexpr (ORD) march_ordered<INTERP, G, SIG, PS>(J, s_tf, R, lane, out, count);
     else if constexpr (Il<SIG>::n > 0 && !PS) march_lanes_il<INTERP, G, SIG>(J, s_tf, R, lane, out, count);
     else march_lanes<INTERP, G, SIG, PS>(J, s_tf, R, lane, out, count);
 }
 
-template <int INTERP, int U, int G, bool PS>
+template <int INTERP, bool ORD, int G, bool PS>
 __device__ __forceinline__ void march_dispatch(const DevJob& J, const float4* __restrict__ s_tf, const RaySetup& R,
                                                int lane, float4& out, int& count) {
     switch (J.sig) {
-    case SIG_F32x1: march_sig<INTERP, U, G, SIG_F32x1, PS>(J, s_tf, R, lane, out, count); break;
-    case SIG_PIC3_F32: march_sig<INTERP, U, G, SIG_PIC3_F32, PS>(J, s_tf, R, lane, out, count); break;
-    case SIG_PIC3_F16: march_sig<INTERP, U, G, SIG_PIC3_F16, PS>(J, s_tf, R, lane, out, count); break;
-    case SIG_PIC3_BF16: march_sig<INTERP, U, G, SIG_PIC3_BF16, PS>(J, s_tf, R, lane, out, count); break;
-    case SIG_IL3: march_sig<INTERP, U, G, SIG_IL3, PS>(J, s_tf, R, lane, out, count); break;
-    case SIG_IL3P: march_sig<INTERP, U, G, SIG_IL3P, PS>(J, s_tf, R, lane, out, count); break;
-    case SIG_IL1: march_sig<INTERP, U, G, SIG_IL1, PS>(J, s_tf, R, lane, out, count); break;
-    case SIG_IL1C: march_sig<INTERP, U, G, SIG_IL1C, PS>(J, s_tf, R, lane, out, count); break;
-    case SIG_IL2: march_sig<INTERP, U, G, SIG_IL2, PS>(J, s_tf, R, lane, out, count); break;
-    case SIG_IL4: march_sig<INTERP, U, G, SIG_IL4, PS>(J, s_tf, R, lane, out, count); break;
-    default: march_sig<INTERP, U, G, SIG_GENERIC, PS>(J, s_tf, R, lane, out, count); break;
+    case SIG_F32x1: march_sig<INTERP, ORD, G, SIG_F32x1, PS>(J, s_tf, R, lane, out, count); break;
+    case SIG_PIC3_F32: march_sig<INTERP, ORD, G, SIG_PIC3_F32, PS>(J, s_tf, R, lane, out, count); break;
+    case SIG_PIC3_F16: march_sig<INTERP, ORD, G, SIG_PIC3_F16, PS>(J, s_tf, R, lane, out, count); break;
+    case SIG_PIC3_BF16: march_sig<INTERP, ORD, G, SIG_PIC3_BF16, PS>(J, s_tf, R, lane, out, count); break;
+    case SIG_IL3: march_sig<INTERP, ORD, G, SIG_IL3, PS>(J, s_tf, R, lane, out, count); break;
+    case SIG_IL3P: march_sig<INTERP, ORD, G, SIG_IL3P, PS>(J, s_tf, R, lane, out, count); break;
+    case SIG_IL1: march_sig<INTERP, ORD, G, SIG_IL1, PS>(J, s_tf, R, lane, out, count); break;
+    case SIG_IL1C: march_sig<INTERP, ORD, G, SIG_IL1C, PS>(J, s_tf, R, lane, out, count); break;
+    case SIG_IL2: march_sig<INTERP, ORD, G, SIG_IL2, PS>(J, s_tf, R, lane, out, count); break;
+    case SIG_IL4: march_sig<INTERP, ORD, G, SIG_IL4, PS>(J, s_tf, R, lane, out, count); break;
+    default: march_sig<INTERP, ORD, G, SIG_GENERIC, PS>(J, s_tf, R, lane, out, count); break;
     }
 }
 
@@ -1102,38 +1126,6 @@ __device__ __forceinline__ float4 iso_shade(const DevJob& J, const float4* __res
     const float light = fmaf(0.7f, fminf(cosine, 1.f), 0.3f);
     const float4 c = classify(s_tf + s * kTfLds, S.iso);
     return make_float4(c.x * light, c.y * light, c.z * light, 1.f);
-}
-
-// One lane per ray: scan points in order, every source at each, until the
-// first crossing.
-template <int INTERP, bool PLAIN>
-__device__ __forceinline__ void march_iso(const DevJob& J, const float4* __restrict__ s_tf, const RaySetup& R,
-                                          float4& out, int& count) {
-    const int dims[3] = {J.dims[0], J.dims[1], J.dims[2]};
-    const float step = (float)J.step;
-    float prev[kMaxSources];
-    int hit = -1, n = 0, k = R.kb;
-    float f = 0.f;
-    for (; k < R.ke; ++k) {
-        float p[3];
-        point_at(J, R, ((float)k + 0.5f) * step, p);
-        ++n;
-        for (int s = 0; s < J.n_src; ++s) {
-            const DevSource& S = J.src[s];
-            const float x = sample_any<INTERP, PLAIN>(S, dims, p);
-            if (hit < 0 && k > R.kb && ((prev[s] >= S.iso) != (x >= S.iso))) {
-                hit = s;
-                f = (S.iso - prev[s]) / (x - prev[s]);
-            }
-            prev[s] = x;
-        }
-        if (hit >= 0) break;
-    }
-    out = make_float4(0.f, 0.f, 0.f, 0.f);
-    count = n;
-    // shade, one source at a time over the lanes whose surface it is
-    for (int s = 0; s < J.n_src; ++s)
-        if (hit == s) out = iso_shade<INTERP, PLAIN>(J, s_tf, R, s, k, f);
 }
 
 // G lanes per ray: lane g takes scan point k0 + g of each row of G points; its
@@ -1219,7 +1211,7 @@ __device__ __forceinline__ bool pixel_of(const DevJob& J, int t, int lane, int w
 // launch has it); SIGK = -1: it dispatches on each job's signature; SIGK = -2:
 // iso-surface jobs; SIGK = -3: iso-surface jobs whose sources are all plain
 // (sample_plain).
-template <int U, int G, int W, int SIGK>
+template <bool ORD, int G, int W, int SIGK>
 __global__ __launch_bounds__(kBlockThreads) __attribute__((amdgpu_waves_per_eu(W > 0 ? W : 1, 8)))
 void raycast_kernel(const DevJob* __restrict__ jobs, const float4* __restrict__ tf_pool, int* __restrict__ cursor,
                     int n_jobs, int total_tiles, int persistent) {
@@ -1281,20 +1273,16 @@ void raycast_kernel(const DevJob* __restrict__ jobs, const float4* __restrict__ 
         float4 c = make_float4(0.f, 0.f, 0.f, 0.f);
         int count = 0;
         if (hit) {
-            if constexpr ((SIGK == -2 || SIGK == -3) && G == 1) {
-                constexpr bool PL = SIGK == -3;
-                if (J.interp) march_iso<1, PL>(J, s_tf, R, c, count);
-                else march_iso<0, PL>(J, s_tf, R, c, count);
-            } else if constexpr (SIGK == -2 || SIGK == -3) {
+            if constexpr (SIGK == -2 || SIGK == -3) {
                 constexpr bool PL = SIGK == -3;
                 if (J.interp) march_iso_lanes<1, G, PL>(J, s_tf, R, lane, c, count);
                 else march_iso_lanes<0, G, PL>(J, s_tf, R, lane, c, count);
             } else if constexpr (SIGK < 0) {
-                if (J.interp) march_dispatch<1, U, G, (W > 0)>(J, s_tf, R, lane, c, count);
-                else march_dispatch<0, U, G, (W > 0)>(J, s_tf, R, lane, c, count);
+                if (J.interp) march_dispatch<1, ORD, G, (W > 0)>(J, s_tf, R, lane, c, count);
+                else march_dispatch<0, ORD, G, (W > 0)>(J, s_tf, R, lane, c, count);
             } else {
-                if (J.interp) march_sig<1, U, G, SIGK, (W > 0)>(J, s_tf, R, lane, c, count);
-                else march_sig<0, U, G, SIGK, (W > 0)>(J, s_tf, R, lane, c, count);
+                if (J.interp) march_sig<1, ORD, G, SIGK, (W > 0)>(J, s_tf, R, lane, c, count);
+                else march_sig<0, ORD, G, SIGK, (W > 0)>(J, s_tf, R, lane, c, count);
             }
         }
         if (in_image && (lane & (G - 1)) == 0) {
@@ -1872,51 +1860,48 @@ __global__ __launch_bounds__(256) void strided_copy_kernel(CopyArgs a) {
 
 using KernelFn = void (*)(const DevJob*, const float4*, int*, int, int, int);
 
+// ordered: the image of one lane per ray, by groups of 4 or 16 lanes
 template <int SIGK>
-KernelFn pick_specialized(int unroll, int lanes, int hint) {
-    if (unroll >= 2) return raycast_kernel<2, 1, 0, SIGK>;
+KernelFn pick_specialized(int ordered, int lanes, int hint) {
+    if (ordered) return lanes == 4 ? raycast_kernel<true, 4, 4, SIGK> : raycast_kernel<true, 16, 4, SIGK>;
     switch (lanes) {
-    case 64: return raycast_kernel<1, 64, 0, SIGK>;
-    case 32: return raycast_kernel<1, 32, 0, SIGK>;
-    case 16: return hint ? raycast_kernel<1, 16, 4, SIGK> : raycast_kernel<1, 16, 0, SIGK>;
-    case 8: return hint ? raycast_kernel<1, 8, 4, SIGK> : raycast_kernel<1, 8, 0, SIGK>;
-    case 4: return hint ? raycast_kernel<1, 4, 4, SIGK> : raycast_kernel<1, 4, 0, SIGK>;
-    case 2: return raycast_kernel<1, 2, 0, SIGK>;
-    default: return hint ? raycast_kernel<1, 1, 4, SIGK> : raycast_kernel<1, 1, 0, SIGK>;
+    case 64: return raycast_kernel<false, 64, 0, SIGK>;
+    case 32: return raycast_kernel<false, 32, 0, SIGK>;
+    case 16: return hint ? raycast_kernel<false, 16, 4, SIGK> : raycast_kernel<false, 16, 0, SIGK>;
+    case 8: return hint ? raycast_kernel<false, 8, 4, SIGK> : raycast_kernel<false, 8, 0, SIGK>;
+    case 4: return hint ? raycast_kernel<false, 4, 4, SIGK> : raycast_kernel<false, 4, 0, SIGK>;
+    default: return raycast_kernel<false, 2, 0, SIGK>;
     }
 }
 
-KernelFn pick_kernel(int mode, int sig, int unroll, int lanes, int hint) {
-    if (mode == 1) {
-        // iso-surface jobs: sig -3 when every source is plain (packed FP32 scalars without
-        // functors, guard layers), else the run-time source handling
-        if (sig == -3) return lanes >= 8 ? raycast_kernel<1, 8, 0, -3> : raycast_kernel<1, 1, 0, -3>;
-        return lanes >= 8 ? raycast_kernel<1, 8, 0, -2> : raycast_kernel<1, 1, 0, -2>;
-    }
+KernelFn pick_kernel(int mode, int sig, int ordered, int lanes, int hint) {
+    // iso-surface jobs: sig -3 when every source is plain (packed FP32 scalars without
+    // functors, guard layers), else the run-time source handling
+    if (mode == 1) return sig == -3 ? raycast_kernel<false, 8, 0, -3> : raycast_kernel<false, 8, 0, -2>;
     switch (sig) {
-    case SIG_F32x1: return pick_specialized<SIG_F32x1>(unroll, lanes, hint);
-    case SIG_PIC3_F32: return pick_specialized<SIG_PIC3_F32>(unroll, lanes, hint);
-    case SIG_PIC3_F16: return pick_specialized<SIG_PIC3_F16>(unroll, lanes, hint);
-    case SIG_PIC3_BF16: return pick_specialized<SIG_PIC3_BF16>(unroll, lanes, hint);
-    case SIG_IL3: return pick_specialized<SIG_IL3>(unroll, lanes, hint);
-    case SIG_IL3P: return pick_specialized<SIG_IL3P>(unroll, lanes, hint);
-    case SIG_IL1: return pick_specialized<SIG_IL1>(unroll, lanes, hint);
-    case SIG_IL1C: return pick_specialized<SIG_IL1C>(unroll, lanes, hint);
-    case SIG_IL2: return pick_specialized<SIG_IL2>(unroll, lanes, hint);
-    case SIG_IL4: return pick_specialized<SIG_IL4>(unroll, lanes, hint);
-    case SIG_GENERIC: return pick_specialized<SIG_GENERIC>(unroll, lanes, 1);
+    case SIG_F32x1: return pick_specialized<SIG_F32x1>(ordered, lanes, hint);
+    case SIG_PIC3_F32: return pick_specialized<SIG_PIC3_F32>(ordered, lanes, hint);
+    case SIG_PIC3_F16: return pick_specialized<SIG_PIC3_F16>(ordered, lanes, hint);
+    case SIG_PIC3_BF16: return pick_specialized<SIG_PIC3_BF16>(ordered, lanes, hint);
+    case SIG_IL3: return pick_specialized<SIG_IL3>(ordered, lanes, hint);
+    case SIG_IL3P: return pick_specialized<SIG_IL3P>(ordered, lanes, hint);
+    case SIG_IL1: return pick_specialized<SIG_IL1>(ordered, lanes, hint);
+    case SIG_IL1C: return pick_specialized<SIG_IL1C>(ordered, lanes, hint);
+    case SIG_IL2: return pick_specialized<SIG_IL2>(ordered, lanes, hint);
+    case SIG_IL4: return pick_specialized<SIG_IL4>(ordered, lanes, hint);
+    case SIG_GENERIC: return pick_specialized<SIG_GENERIC>(ordered, lanes, 1);
     default:
         break;
     }
     // mixed signatures: the dispatching kernels (one lane-count each)
+    if (ordered) return lanes == 4 ? raycast_kernel<true, 4, 4, -1> : raycast_kernel<true, 16, 4, -1>;
     switch (lanes) {
-    case 64: return raycast_kernel<1, 64, 0, -1>;
-    case 32: return raycast_kernel<1, 32, 0, -1>;
-    case 16: return raycast_kernel<1, 16, 0, -1>;
-    case 8: return raycast_kernel<1, 8, 0, -1>;
-    case 4: return raycast_kernel<1, 4, 0, -1>;
-    case 2: return raycast_kernel<1, 2, 0, -1>;
-    default: return raycast_kernel<1, 1, 0, -1>;
+    case 64: return raycast_kernel<false, 64, 0, -1>;
+    case 32: return raycast_kernel<false, 32, 0, -1>;
+    case 16: return raycast_kernel<false, 16, 0, -1>;
+    case 8: return raycast_kernel<false, 8, 0, -1>;
+    case 4: return raycast_kernel<false, 4, 0, -1>;
+    default: return raycast_kernel<false, 2, 0, -1>;
     }
 }
 
@@ -1943,7 +1928,7 @@ int launch_raycast(const LaunchArgs& a, void* stream) {
     const size_t lds = (size_t)(a.max_src > 0 ? a.max_src : 1) * kTfLds * sizeof(float4);
     const unsigned blocks = a.persistent ? (unsigned)a.grid : (unsigned)a.total_tiles;
     if (blocks == 0) return hipGetLastError();
-    const KernelFn kernel = pick_kernel(a.mode, a.sig, a.unroll, a.lanes, a.waves_hint);
+    const KernelFn kernel = pick_kernel(a.mode, a.sig, a.ordered, a.lanes, a.waves_hint);
     hipLaunchKernelGGL(kernel, dim3(blocks), dim3(kBlockThreads), lds, (hipStream_t)stream, a.jobs,
                        reinterpret_cast<const float4*>(a.tf_pool), a.cursor, a.n_jobs, a.total_tiles, a.persistent);
     return hipGetLastError();
@@ -2122,7 +2107,7 @@ int noalloc_scratch(int device, void** ptr) {
 }
 
 int raycast_occupancy(int* blocks_per_cu) {
-    return hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks_per_cu, raycast_kernel<1, 1, 0, -1>, kBlockThreads,
+    return hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks_per_cu, raycast_kernel<false, 4, 0, -1>, kBlockThreads,
                                                        3 * kTfLds * sizeof(float4));
 }
 
