@@ -215,8 +215,8 @@ typedef struct {
 } isaac_render_desc;
 
 /* Ray-cast jobs (all validated before any launch).  One job is one kernel
- * launch over its image; several jobs form one persistent launch over a
- * shared tile queue, replayed as a hipGraph unless ISAAC_NO_GRAPH.  Without
+ * launch over its image; several jobs form one launch over the tiles of all
+ * their images, replayed as a hipGraph unless ISAAC_NO_GRAPH.  Without
  * ISAAC_ASYNC the call returns after the images are complete.
  * Derived volume: when the call's expected scan points on a volume (8 voxel
  * visits each under trilinear interpolation) exceed 4 per voxel, or with

@@ -4,7 +4,7 @@
 // functor chains to bytecode, baking transfer tables, building per-job
 // parameter blocks (camera basis in FP64, clip planes, active sources),
 // staging them through pinned memory, launching the kernels of raycast.hip,
-// batching jobs into persistent launches replayed as hipGraphs, and the
+// batching jobs into single launches replayed as hipGraphs, and the
 // library-owned output images of the serving calls.
 #include <hip/hip_runtime.h>
 
@@ -97,13 +97,12 @@ struct TfSlot {
 struct RingSlot {
     DevJob* host = nullptr;         // pinned
     DevJob* dev = nullptr;
-    int* cursor = nullptr;
     hipEvent_t done = nullptr;
     bool busy = false;
     // graph cache
     hipGraphExec_t exec = nullptr;
     hipGraph_t graph = nullptr;
-    int g_jobs = -1, g_tiles = -1, g_grid = -1, g_src = -1, g_ordered = -1, g_lanes = -1, g_hint = -1, g_sig = -3;
+    int g_jobs = -1, g_tiles = -1, g_src = -1, g_ordered = -1, g_lanes = -1, g_hint = -1, g_sig = -3;
     unsigned g_fill = 0;
     int g_dense = -1;
 };
@@ -199,7 +198,6 @@ struct isaac_context {
     std::vector<hipStream_t> serve_streams;
     int serve_rr = 0;
     int n_cu = 0;
-    int blocks_per_cu = 1;
     size_t budget = 0, used = 0;
     int max_inflight = 64;
     std::vector<Volume> volumes;
@@ -706,9 +704,6 @@ isaac_status enqueue_jobs(isaac_context* ctx, const isaac_render_desc* jobs, con
     la.n_jobs = n;
     la.total_tiles = tiles;
     la.tf_pool = ctx->tf_pool;
-    la.cursor = r->cursor;
-    la.persistent = n > 1 ? 1 : 0;
-    la.grid = std::max(1, ctx->n_cu * ctx->blocks_per_cu);
     la.max_src = std::max(1, max_src);
     la.ordered = ordered ? 1 : 0;
     la.lanes = lanes;
@@ -780,7 +775,7 @@ isaac_status enqueue_jobs(isaac_context* ctx, const isaac_render_desc* jobs, con
     }
     const bool use_graph = n > 1 && !(flags & ISAAC_NO_GRAPH) && !noalloc;
     if (use_graph) {
-        if (!r->exec || r->g_jobs != n || r->g_tiles != tiles || r->g_grid != la.grid || r->g_src != la.max_src ||
+        if (!r->exec || r->g_jobs != n || r->g_tiles != tiles || r->g_src != la.max_src ||
             r->g_ordered != la.ordered || r->g_lanes != la.lanes || r->g_hint != la.waves_hint || r->g_sig != la.sig ||
             r->g_fill != la.fill_blocks || r->g_dense != la.dense_setup) {
             if (r->exec) hipGraphExecDestroy(r->exec);
@@ -789,7 +784,6 @@ isaac_status enqueue_jobs(isaac_context* ctx, const isaac_render_desc* jobs, con
             r->graph = nullptr;
             HIP_TRY(ctx, hipStreamBeginCapture(ctx->cap_stream, hipStreamCaptureModeThreadLocal));
             hipError_t e = hipMemcpyAsync(r->dev, r->host, sizeof(DevJob) * n, hipMemcpyHostToDevice, ctx->cap_stream);
-            if (e == hipSuccess) e = (hipError_t)launch_reset_counter(r->cursor, ctx->cap_stream);
             if (e == hipSuccess) e = (hipError_t)launch_prepass(la, ctx->cap_stream);
             if (e == hipSuccess) e = (hipError_t)launch_raycast(la, ctx->cap_stream);
             hipGraph_t g = nullptr;
@@ -803,7 +797,6 @@ isaac_status enqueue_jobs(isaac_context* ctx, const isaac_render_desc* jobs, con
             HIP_TRY(ctx, hipGraphInstantiate(&r->exec, g, nullptr, nullptr, 0));
             r->g_jobs = n;
             r->g_tiles = tiles;
-            r->g_grid = la.grid;
             r->g_src = la.max_src;
             r->g_ordered = la.ordered;
             r->g_lanes = la.lanes;
@@ -828,16 +821,11 @@ isaac_status enqueue_jobs(isaac_context* ctx, const isaac_render_desc* jobs, con
         if (t1) HIP_TRY(ctx, hipEventRecord(t1, stream));
     } else {
         int rc = hipSuccess;
-        if (n == 1 && !la.persistent) {
+        if (n == 1) {
             // the job block travels as the prepass's kernel argument and is stored by it
             rc = launch_prepass_one(r->host[0], r->dev, la.fill_blocks, la.dense_setup, stream);
         } else {
             HIP_TRY(ctx, hipMemcpyAsync(r->dev, r->host, sizeof(DevJob) * n, hipMemcpyHostToDevice, stream));
-            if (la.persistent) {
-                rc = launch_reset_counter(r->cursor, stream);
-                if (rc != hipSuccess)
-                    return set_err(ctx, ISAAC_ERR_DEVICE, "counter reset: %s", hipGetErrorString((hipError_t)rc));
-            }
             rc = launch_prepass(la, stream);
         }
         if (rc != hipSuccess) return set_err(ctx, ISAAC_ERR_DEVICE, "prepass launch: %s", hipGetErrorString((hipError_t)rc));
@@ -1241,8 +1229,6 @@ isaac_status isaac_init(const isaac_init_desc* desc, isaac_context** out) {
         const int rc = noalloc_scratch(d.device, &ctx->noalloc_scratch);   // d.device is current
         if (rc != hipSuccess) return fail("scratch symbol address", (hipError_t)rc);
     }
-    int bpc = 1;
-    if (raycast_occupancy(&bpc) == hipSuccess && bpc > 0) ctx->blocks_per_cu = bpc;
     if (d.stream) {
         ctx->stream = static_cast<hipStream_t>(d.stream);
     } else if (d.flags & ISAAC_INIT_NULL_STREAM) {
@@ -1264,8 +1250,6 @@ isaac_status isaac_init(const isaac_init_desc* desc, isaac_context** out) {
         RingSlot& r = ctx->ring[i];
         e = hipHostMalloc((void**)&r.host, sizeof(DevJob) * kMaxBatch);
         if (e == hipSuccess) e = hipMalloc((void**)&r.dev, sizeof(DevJob) * kMaxBatch);
-        if (e == hipSuccess) e = hipMalloc((void**)&r.cursor, 64);
-        if (e == hipSuccess) e = hipMemset(r.cursor, 0, 64);
         if (e == hipSuccess) e = hipEventCreateWithFlags(&r.done, hipEventDisableTiming);
         if (e != hipSuccess) return fail("staging ring", e);
     }
@@ -1304,7 +1288,6 @@ void isaac_destroy(isaac_context* ctx) {
         if (r.graph) hipGraphDestroy(r.graph);
         if (r.host) hipHostFree(r.host);
         if (r.dev) hipFree(r.dev);
-        if (r.cursor) hipFree(r.cursor);
         if (r.done) hipEventDestroy(r.done);
     }
     for (auto& p : ctx->pending) hipEventDestroy(p.ev);

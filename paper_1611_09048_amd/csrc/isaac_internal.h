@@ -132,9 +132,6 @@ struct LaunchArgs {
     int n_jobs;
     int total_tiles;
     const float* tf_pool;      // device, [slot][256][4]
-    int* cursor;               // device work counter (persistent mode)
-    int persistent;            // 0: one workgroup per tile; 1: grid-stride over a tile queue
-    int grid;                  // workgroups launched in persistent mode
     int max_src;               // widest job's active source count (sizes the LDS tables)
     int ordered;               // 1: jobs of one lane per ray, evaluated by groups of `lanes` (4 or 16) lanes
     int lanes;                 // lanes per ray (kernel variant)
@@ -150,7 +147,6 @@ int launch_prepass(const LaunchArgs& a, void* stream);               // fill out
 // (the device job block the ray-casting launch reads).
 int launch_prepass_one(const DevJob& job, DevJob* dst, unsigned fill_blocks, int dense, void* stream);
 int launch_raycast(const LaunchArgs& a, void* stream);               // returns hipError_t
-int launch_reset_counter(int* counter, void* stream);
 // Pooled schedule of one job (lanes >= 2): ray setup with compaction into
 // `rays` (ray_record_bytes() per pixel), then a resident kernel handing the
 // compacted rays to lane groups.  counters: 2 device ints.
@@ -160,7 +156,6 @@ size_t ray_record_bytes();
 int launch_strided_copy(const void* const* src_comp, const int64_t* src_stride, void* dst,
                         const int64_t* dst_stride, int esize, int f_dim, const int32_t lo[3],
                         const int32_t ext[3], void* stream);
-int raycast_occupancy(int* blocks_per_cu);
 // Device scratch of the render calls that allocate nothing (ray records of the
 // set-up pass): a static array of kNoAllocScratchBytes per device.  Looks up the
 // current device's copy (call with `device` current) once per device; *ptr is

@@ -18,6 +18,8 @@
 // Transfer tables (256 x RGBA32F per source) live in LDS.
 #include <hip/hip_runtime.h>
 
+#include <limits.h>
+
 #include <algorithm>
 #include <mutex>
 
@@ -950,6 +952,14 @@ __device__ __forceinline__ void group_scan(int lane, float& c0, float& c1, float
 // the last point's sample): the scan is inclusive, so no kept lane's prefix
 // depends on it, the termination ballot masks it, and the lane taken is never
 // past the row's last kept point.
+// The lane index, opaque to the optimizer: masks and permute addresses made from
+// it inside a loop are recomputed there (one instruction each) instead of held in
+// registers through it.
+__device__ __forceinline__ int fresh(int lane) {
+    asm volatile("" : "+v"(lane));
+    return lane;
+}
+
 template <int G>
 __device__ __forceinline__ bool row_composite(const DevJob& J, const RaySetup& R, int lane, int k0, bool valid,
                                               float c0, float c1, float c2, float a, RayAccum& acc) {
@@ -958,7 +968,8 @@ __device__ __forceinline__ bool row_composite(const DevJob& J, const RaySetup& R
     const float n0 = fmaf(T, c0, acc.C0), n1 = fmaf(T, c1, acc.C1), n2 = fmaf(T, c2, acc.C2), na = fmaf(T, a, acc.A);
     const unsigned long long m = __builtin_amdgcn_ballot_w64(na >= J.ert) & __builtin_amdgcn_ballot_w64(valid);
     constexpr unsigned long long kGroupMask = G == 64 ? ~0ull : ((1ull << (G & 63)) - 1ull);
-    const unsigned long long bits = (m >> (lane & ~(G - 1))) & kGroupMask;
+    const int first = fresh(lane) & ~(G - 1);
+    const unsigned long long bits = (m >> first) & kGroupMask;
     const bool stop = bits != 0;
     // the first terminating point, else the row's last kept one (k0 < R.ke, so
     // last >= 0; every set bit belongs to a kept point, i.e. lies at or below last)
@@ -967,10 +978,13 @@ __device__ __forceinline__ bool row_composite(const DevJob& J, const RaySetup& R
     if constexpr (G <= 32) sel = __builtin_ctz((unsigned)bits | (1u << last));
     else sel = __builtin_ctzll(bits | (1ull << last));
     acc.n += sel + 1;
-    acc.C0 = __shfl(n0, sel, G);
-    acc.C1 = __shfl(n1, sel, G);
-    acc.C2 = __shfl(n2, sel, G);
-    acc.A = __shfl(na, sel, G);
+    auto from = [&](float x) {
+        return __builtin_bit_cast(float, __builtin_amdgcn_ds_bpermute((first + sel) << 2, __builtin_bit_cast(int, x)));
+    };
+    acc.C0 = from(n0);
+    acc.C1 = from(n1);
+    acc.C2 = from(n2);
+    acc.A = from(na);
     return stop || k0 + G >= R.ke;
 }
 
@@ -979,8 +993,7 @@ __device__ __forceinline__ bool row_composite(const DevJob& J, const RaySetup& R
 template <int INTERP, int G, int SIG, bool PS>
 __device__ __forceinline__ bool lanes_row(const DevJob& J, const float4* __restrict__ s_tf, const RaySetup& R,
                                           int lane, int k0, RayAccum& acc) {
-    const int g = lane & (G - 1);
-    const int k = k0 + g;
+    const int k = k0 + (fresh(lane) & (G - 1));
     const bool valid = k < R.ke;
     float E[3], S;
     point<INTERP, SIG, PS>(J, s_tf, R, valid ? k : R.ke - 1, E, S);
@@ -1204,93 +1217,86 @@ __device__ __forceinline__ bool pixel_of(const DevJob& J, int t, int lane, int w
     return px <= J.cull[2] && py <= J.cull[3];
 }
 
+// One workgroup per tile, for one job or the tiles of many.  (Batches once ran a
+// resident set of workgroups over a tile queue, to stage a job's tables once for
+// many tiles: 1303 against 1256 us a call for 64 sub-volumes, 533 against 439 us for
+// six served requests of one volume, 2 % the other way for 40 small ones.)
 // Waves-per-SIMD hint: W = 0 leaves register allocation to the compiler and
 // issues every load of a scan point at once; W > 0 asks for at least W
-// resident waves per SIMD and evaluates the sources one after another.
+// resident waves per SIMD and evaluates the sources one after another.  The
+// loops over up to three adjacent values need no bound: they fit the 64 vector
+// registers of 8 waves, since what a row needs of the lane index is made afresh
+// (fresh()) and the pixel is not kept through the loop.
 // SIGK >= 0: the kernel runs only that source signature (every job of the
 // launch has it); SIGK = -1: it dispatches on each job's signature; SIGK = -2:
 // iso-surface jobs; SIGK = -3: iso-surface jobs whose sources are all plain
 // (sample_plain).
 template <bool ORD, int G, int W, int SIGK>
 __global__ __launch_bounds__(kBlockThreads) __attribute__((amdgpu_waves_per_eu(W > 0 ? W : 1, 8)))
-void raycast_kernel(const DevJob* __restrict__ jobs, const float4* __restrict__ tf_pool, int* __restrict__ cursor,
-                    int n_jobs, int total_tiles, int persistent) {
+void raycast_kernel(const DevJob* __restrict__ jobs, const float4* __restrict__ tf_pool, int n_jobs, int tile0) {
     extern __shared__ float4 s_tf[];
-    __shared__ int s_tile;
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    int cur_job = -1;
-    for (int iter = 0;; ++iter) {
-        int tile;
-        if (persistent) {
-            if (threadIdx.x == 0) s_tile = atomicAdd(cursor, 1);
-            __syncthreads();
-            tile = s_tile;
-            __syncthreads();
-            if (tile >= total_tiles) break;
-        } else {
-            if (iter > 0) break;
-            tile = (int)blockIdx.x;
-        }
-        tile = __builtin_amdgcn_readfirstlane(tile);
-        const int job = __builtin_amdgcn_readfirstlane(find_job(jobs, n_jobs, tile));
-        const DevJob& J = jobs[job];
-        // tiles cover the box's screen rectangle only (the fill kernel clears the rest)
-        int px = 0, py = 0;
-        const bool in_image = pixel_of<G>(J, tile - J.tile_begin, lane, wave, px, py);
-        RaySetup R;
-        bool hit;
-        if (J.rays) {
-            // set up by the prepass, one lane per ray
-            hit = false;
-            if (in_image) {
-                const int rw = J.cull[2] - J.cull[0] + 1;
-                const RayRec& rr = static_cast<const RayRec*>(J.rays)[(py - J.cull[1]) * rw + (px - J.cull[0])];
-                R.kb = rr.kb;
-                R.ke = rr.ke;
-                hit = R.kb < R.ke;
-                if (hit) {
-                    for (int a = 0; a < 3; ++a) {
-                        R.pb[a] = rr.pb[a];
-                        R.d[a] = rr.d[a];
-                    }
-                    R.t_first = rr.t_first;
+    const int tile = tile0 + (int)blockIdx.x;
+    const DevJob& J = jobs[__builtin_amdgcn_readfirstlane(find_job(jobs, n_jobs, tile))];
+    // tiles cover the box's screen rectangle only (the fill kernel clears the rest)
+    int px = 0, py = 0;
+    const bool in_image = pixel_of<G>(J, tile - J.tile_begin, lane, wave, px, py);
+    RaySetup R;
+    bool hit;
+    if (J.rays) {
+        // set up by the prepass, one lane per ray
+        hit = false;
+        if (in_image) {
+            const int rw = J.cull[2] - J.cull[0] + 1;
+            const RayRec& rr = static_cast<const RayRec*>(J.rays)[(py - J.cull[1]) * rw + (px - J.cull[0])];
+            R.kb = rr.kb;
+            R.ke = rr.ke;
+            hit = R.kb < R.ke;
+            if (hit) {
+                for (int a = 0; a < 3; ++a) {
+                    R.pb[a] = rr.pb[a];
+                    R.d[a] = rr.d[a];
                 }
+                R.t_first = rr.t_first;
             }
+        }
+    } else {
+        hit = in_image && setup_ray(J, px, py, R);
+    }
+    if (J.out_depth && in_image && (lane & (G - 1)) == 0)
+        J.out_depth[(size_t)py * J.width + px] = hit ? R.t_first : __builtin_inff();
+    // tiles no ray of which meets the box skip the transfer tables
+    if (__syncthreads_or(hit)) {
+        const int n = J.n_src * kTfLds;
+        for (int i = threadIdx.x; i < n; i += kBlockThreads) {
+            const int s = i / kTfLds, e = min(i % kTfLds, kTfEntries - 1);
+            s_tf[i] = tf_pool[(size_t)J.src[s].tf_slot * kTfRows + 2 * e];
+        }
+        __syncthreads();
+    }
+    float4 c = make_float4(0.f, 0.f, 0.f, 0.f);
+    int count = 0;
+    if (hit) {
+        if constexpr (SIGK == -2 || SIGK == -3) {
+            constexpr bool PL = SIGK == -3;
+            if (J.interp) march_iso_lanes<1, G, PL>(J, s_tf, R, lane, c, count);
+            else march_iso_lanes<0, G, PL>(J, s_tf, R, lane, c, count);
+        } else if constexpr (SIGK < 0) {
+            if (J.interp) march_dispatch<1, ORD, G, (W > 0)>(J, s_tf, R, lane, c, count);
+            else march_dispatch<0, ORD, G, (W > 0)>(J, s_tf, R, lane, c, count);
         } else {
-            hit = in_image && setup_ray(J, px, py, R);
+            if (J.interp) march_sig<1, ORD, G, SIGK, (W > 0)>(J, s_tf, R, lane, c, count);
+            else march_sig<0, ORD, G, SIGK, (W > 0)>(J, s_tf, R, lane, c, count);
         }
-        // tiles no ray of which meets the box skip the transfer tables; the
-        // barrier also ends every read of the previous tile's tables
-        if (__syncthreads_or(hit) && job != cur_job) {
-            const int n = J.n_src * kTfLds;
-            for (int i = threadIdx.x; i < n; i += kBlockThreads) {
-                const int s = i / kTfLds, e = min(i % kTfLds, kTfEntries - 1);
-                s_tf[i] = tf_pool[(size_t)J.src[s].tf_slot * kTfRows + 2 * e];
-            }
-            __syncthreads();
-            cur_job = job;
-        }
-        float4 c = make_float4(0.f, 0.f, 0.f, 0.f);
-        int count = 0;
-        if (hit) {
-            if constexpr (SIGK == -2 || SIGK == -3) {
-                constexpr bool PL = SIGK == -3;
-                if (J.interp) march_iso_lanes<1, G, PL>(J, s_tf, R, lane, c, count);
-                else march_iso_lanes<0, G, PL>(J, s_tf, R, lane, c, count);
-            } else if constexpr (SIGK < 0) {
-                if (J.interp) march_dispatch<1, ORD, G, (W > 0)>(J, s_tf, R, lane, c, count);
-                else march_dispatch<0, ORD, G, (W > 0)>(J, s_tf, R, lane, c, count);
-            } else {
-                if (J.interp) march_sig<1, ORD, G, SIGK, (W > 0)>(J, s_tf, R, lane, c, count);
-                else march_sig<0, ORD, G, SIGK, (W > 0)>(J, s_tf, R, lane, c, count);
-            }
-        }
-        if (in_image && (lane & (G - 1)) == 0) {
-            const size_t pix = (size_t)py * J.width + px;
-            reinterpret_cast<float4*>(J.out)[pix] = c;
-            if (J.out_samples) J.out_samples[pix] = count;
-            if (J.out_depth) J.out_depth[pix] = hit ? R.t_first : __builtin_inff();
-        }
+    }
+    // the pixel again, from the thread index: nothing of it stays in registers
+    // through the loop above
+    int tid = (int)threadIdx.x;
+    asm("" : "+v"(tid));
+    if (pixel_of<G>(J, tile - J.tile_begin, tid & 63, tid >> 6, px, py) && (tid & (G - 1)) == 0) {
+        const size_t pix = (size_t)py * J.width + px;
+        reinterpret_cast<float4*>(J.out)[pix] = c;
+        if (J.out_samples) J.out_samples[pix] = count;
     }
 }
 
@@ -1858,12 +1864,13 @@ __global__ __launch_bounds__(256) void strided_copy_kernel(CopyArgs a) {
 
 }  // namespace
 
-using KernelFn = void (*)(const DevJob*, const float4*, int*, int, int, int);
+using KernelFn = void (*)(const DevJob*, const float4*, int, int);
 
 // ordered: the image of one lane per ray, by groups of 4 or 16 lanes
 template <int SIGK>
 KernelFn pick_specialized(int ordered, int lanes, int hint) {
-    if (ordered) return lanes == 4 ? raycast_kernel<true, 4, 4, SIGK> : raycast_kernel<true, 16, 4, SIGK>;
+    constexpr int W = SIGK == SIG_GENERIC ? 0 : 4;      // the general loop would spill under a bound of 4 waves
+    if (ordered) return lanes == 4 ? raycast_kernel<true, 4, W, SIGK> : raycast_kernel<true, 16, W, SIGK>;
     switch (lanes) {
     case 64: return raycast_kernel<false, 64, 0, SIGK>;
     case 32: return raycast_kernel<false, 32, 0, SIGK>;
@@ -1894,7 +1901,7 @@ KernelFn pick_kernel(int mode, int sig, int ordered, int lanes, int hint) {
         break;
     }
     // mixed signatures: the dispatching kernels (one lane-count each)
-    if (ordered) return lanes == 4 ? raycast_kernel<true, 4, 4, -1> : raycast_kernel<true, 16, 4, -1>;
+    if (ordered) return lanes == 4 ? raycast_kernel<true, 4, 0, -1> : raycast_kernel<true, 16, 0, -1>;
     switch (lanes) {
     case 64: return raycast_kernel<false, 64, 0, -1>;
     case 32: return raycast_kernel<false, 32, 0, -1>;
@@ -1926,11 +1933,14 @@ int launch_prepass_one(const DevJob& job, DevJob* dst, unsigned fill_blocks, int
 int launch_raycast(const LaunchArgs& a, void* stream) {
     // dynamic LDS: one staged table (kTfLds RGBA32F values) per active source of the widest job
     const size_t lds = (size_t)(a.max_src > 0 ? a.max_src : 1) * kTfLds * sizeof(float4);
-    const unsigned blocks = a.persistent ? (unsigned)a.grid : (unsigned)a.total_tiles;
-    if (blocks == 0) return hipGetLastError();
     const KernelFn kernel = pick_kernel(a.mode, a.sig, a.ordered, a.lanes, a.waves_hint);
-    hipLaunchKernelGGL(kernel, dim3(blocks), dim3(kBlockThreads), lds, (hipStream_t)stream, a.jobs,
-                       reinterpret_cast<const float4*>(a.tf_pool), a.cursor, a.n_jobs, a.total_tiles, a.persistent);
+    constexpr int kMaxBlocks = 1 << 23;      // a grid holds fewer than 2^32 threads
+    for (int tile0 = 0; tile0 < a.total_tiles; tile0 += kMaxBlocks) {
+        hipLaunchKernelGGL(kernel, dim3((unsigned)std::min(kMaxBlocks, a.total_tiles - tile0)), dim3(kBlockThreads),
+                           lds, (hipStream_t)stream, a.jobs, reinterpret_cast<const float4*>(a.tf_pool), a.n_jobs,
+                           tile0);
+        if (tile0 > INT_MAX - kMaxBlocks) break;
+    }
     return hipGetLastError();
 }
 
@@ -1983,11 +1993,6 @@ int launch_raycast_pooled(const DevJob* job_dev, int width, int height, const fl
 }
 
 size_t ray_record_bytes() { return sizeof(RayRec); }
-
-int launch_reset_counter(int* counter, void* stream) {
-    hipLaunchKernelGGL(reset_counter_kernel, dim3(1), dim3(64), 0, (hipStream_t)stream, counter, 1);
-    return hipGetLastError();
-}
 
 int launch_strided_copy(const void* const* src_comp, const int64_t* src_stride, void* dst,
                         const int64_t* dst_stride, int esize, int f_dim, const int32_t lo[3],
@@ -2104,11 +2109,6 @@ int noalloc_scratch(int device, void** ptr) {
     }
     *ptr = addr[device];
     return hipSuccess;
-}
-
-int raycast_occupancy(int* blocks_per_cu) {
-    return hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks_per_cu, raycast_kernel<false, 4, 0, -1>, kBlockThreads,
-                                                       3 * kTfLds * sizeof(float4));
 }
 
 }  // namespace isaac
