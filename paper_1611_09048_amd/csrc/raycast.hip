@@ -1886,17 +1886,30 @@ __global__ __launch_bounds__(256) void strided_copy_kernel(CopyArgs a) {
 
 using KernelFn = void (*)(const DevJob*, const float4*, int, int);
 
+// The variant (W) of a signature's loop under the hint for at least 4 waves per
+// SIMD.  One or two adjacent values: the pipelined loop (54 and 74 vector
+// registers, 8 and 6 waves) is the faster one (two derived sources at 720p 81
+// against 88 us a call, a 48^3 scalar 20.7 against 22.4).  Scalar and vectors read
+// in place: every source's loads together (104 registers, 4 waves) instead of a
+// source after the other: 272 against 350 us for 192^3 FP32 at 1024 x 768.  Three
+// and four adjacent values keep the loop with more waves (six served requests 587
+// against 613 us, four derived sources 76 against 79), the general loop its bound.
+template <int SIGK>
+constexpr int kHintW = Il<SIGK>::n >= 3 || SIGK == SIG_GENERIC ? 4 : 0;
+
 // ordered: the image of one lane per ray, by groups of 4 or 16 lanes
 template <int SIGK>
 KernelFn pick_specialized(int ordered, int lanes, int hint) {
-    constexpr int W = SIGK == SIG_GENERIC ? 0 : 4;      // the general loop would spill under a bound of 4 waves
+    // neither the general loop nor sources read in place under a bound of 4 waves (one would spill, the other: above)
+    constexpr int W = SIGK <= SIG_PIC3_BF16 ? 0 : 4;
+    constexpr int H = kHintW<SIGK>;
     if (ordered) return lanes == 4 ? raycast_kernel<true, 4, W, SIGK> : raycast_kernel<true, 16, W, SIGK>;
     switch (lanes) {
     case 64: return raycast_kernel<false, 64, 0, SIGK>;
     case 32: return raycast_kernel<false, 32, 0, SIGK>;
-    case 16: return hint ? raycast_kernel<false, 16, 4, SIGK> : raycast_kernel<false, 16, 0, SIGK>;
-    case 8: return hint ? raycast_kernel<false, 8, 4, SIGK> : raycast_kernel<false, 8, 0, SIGK>;
-    case 4: return hint ? raycast_kernel<false, 4, 4, SIGK> : raycast_kernel<false, 4, 0, SIGK>;
+    case 16: return hint ? raycast_kernel<false, 16, H, SIGK> : raycast_kernel<false, 16, 0, SIGK>;
+    case 8: return hint ? raycast_kernel<false, 8, H, SIGK> : raycast_kernel<false, 8, 0, SIGK>;
+    case 4: return hint ? raycast_kernel<false, 4, H, SIGK> : raycast_kernel<false, 4, 0, SIGK>;
     default: return raycast_kernel<false, 2, 0, SIGK>;
     }
 }
