@@ -11,17 +11,19 @@
 //              counted per table in LDS;
 //   (host)     Huffman code lengths and codes per table (Annex K.2);
 //   3. bits:   the same symbols priced with the codes: bits per block and per
-//              workgroup (16 blocks);
-//   4. scan:   one workgroup turns the workgroup bit counts into bit offsets;
-//   5. pack:   each workgroup ORs its 16 blocks' codes into an LDS image of its
-//              bit range (lane offsets from a wave prefix sum), stores the words
-//              it owns alone and ORs in the two it may share with its neighbours;
-//              the last block adds the 1-bit padding to a byte boundary;
-//   6. stuff:  per 16 KB of stream the 0xFF count, a prefix sum over those, and
-//              the copy that inserts a 0x00 after every 0xFF (staged in LDS, so
-//              the stores are contiguous).
-// The host reads the symbol counts once to build the tables, then the two
-// totals (bits, stuffed bytes), and copies the coded bytes behind the headers.
+//              workgroup (32 blocks);
+//   4. pack:   each workgroup sums the bit counts of the workgroups before it (its
+//              bit offset), ORs its 32 blocks' codes into an LDS image of its bit
+//              range (lane offsets from a wave prefix sum), stores the words it owns
+//              alone and ORs in the two it may share with its neighbours (the words
+//              are zero between frames); the last one adds the 1-bit padding to a
+//              byte boundary;
+//   5. stuff:  per 4 KB of stream the 0xFF count, then the copy that inserts a 0x00
+//              after every 0xFF (staged in LDS, so the stores are contiguous),
+//              straight into pinned host memory, with the totals.
+// The host reads the symbol counts once to build the tables, then finds the coded
+// bytes in place: the device writes both to pinned memory itself, since a copy
+// enqueued after a wait costs more (about 40 us) than the passes it waits for.
 // Scratch is sized for the largest possible stream of the frame, so no pass
 // waits for the host to learn the actual size.
 
@@ -53,6 +55,12 @@ constexpr int kStuffPerThread = 16;       // bytes of stream per thread in the s
 constexpr int kStuffChunk = kThreads * kStuffPerThread;
 constexpr int kHistCopies = 64;           // symbol counts kept in this many copies: fewer atomics per address
 constexpr int kTopItems = 16;             // items per thread of the one-workgroup prefix sum
+// A workgroup finds its offset by summing the counts before it, which all of them
+// together do in n^2 / 2 reads from the L2 (3038 groups at 1920 x 1080: 37 MB), up to
+// these many counts; beyond, one workgroup scans them first.
+constexpr long long kMaxSummedGroups = 8192;
+constexpr long long kMaxSummedChunks = 65536;   // of the largest stream; a frame's is a small part of it
+constexpr long long kStuffGrid = 1024;
 
 __device__ inline int category(int v) { return v ? 32 - __clz(v < 0 ? -v : v) : 0; }
 
@@ -310,13 +318,11 @@ __global__ __launch_bounds__(kThreads) void jpeg_bits_kernel(const int16_t* __re
     }
 }
 
-// ---- 4. one workgroup: exclusive prefix sum in place, total behind ----
-// With `words`, also clears the stream word at every start offset that is not
-// word aligned: the two workgroups meeting there both OR into it.
+// ---- one workgroup: exclusive prefix sum in place (frames of very many groups) ----
 
 __global__ __launch_bounds__(kThreads) void scan_top_kernel(unsigned long long* __restrict__ part, long long n_parts,
-                                                            unsigned long long* __restrict__ total,
-                                                            uint32_t* __restrict__ words) {
+                                                            const unsigned long long* __restrict__ n_live) {
+    if (n_live) n_parts = min(n_parts, (long long)(((*n_live + 7) / 8 + kStuffChunk - 1) / kStuffChunk));
     unsigned long long carry = 0;
     for (long long c0 = 0; c0 < n_parts; c0 += (long long)kThreads * kTopItems) {
         const long long i0 = c0 + (long long)threadIdx.x * kTopItems;
@@ -330,15 +336,33 @@ __global__ __launch_bounds__(kThreads) void scan_top_kernel(unsigned long long* 
         for (int k = 0; k < kTopItems; ++k)
             if (i0 + k < n_parts) {
                 part[i0 + k] = ex;
-                if (words && (ex & 31)) words[ex >> 5] = 0u;
                 ex += v[k];
             }
         carry += all;
     }
-    if (threadIdx.x == 0) *total = carry;
 }
 
-// ---- 5. bit packing ----
+// Sum of part[0 .. n), on every thread of the workgroup.
+__device__ inline unsigned long long block_sum_before(const unsigned long long* __restrict__ part, long long n) {
+    unsigned long long v = 0, all;
+    for (long long i = threadIdx.x; i < n; i += kThreads) v += part[i];
+    block_excl_scan(v, &all);
+    return all;
+}
+
+// The frame's codes and code lengths from pinned host memory.
+__global__ __launch_bounds__(kThreads) void jpeg_tables_kernel(const uint32_t* __restrict__ host_codes,
+                                                               const uint32_t* __restrict__ host_lens,
+                                                               uint32_t* __restrict__ codes,
+                                                               uint32_t* __restrict__ lens) {
+    uint32_t c[kJpegTableCount];
+    for (int k = 0; k < kJpegTableCount; ++k) c[k] = host_codes[k * kThreads + threadIdx.x];
+    const uint32_t l = host_lens[threadIdx.x];
+    for (int k = 0; k < kJpegTableCount; ++k) codes[k * kThreads + threadIdx.x] = c[k];
+    lens[threadIdx.x] = l;
+}
+
+// ---- 4. bit packing ----
 
 // OR n (1..32) bits of val, most significant first, in at bit position q of W.
 __device__ inline void lds_put(uint32_t* W, int q, uint32_t val, int n) {
@@ -355,8 +379,9 @@ __device__ inline void lds_put(uint32_t* W, int q, uint32_t val, int n) {
 __global__ __launch_bounds__(kThreads) void jpeg_pack_kernel(const int16_t* __restrict__ coef, int n_blocks,
                                                              const uint32_t* __restrict__ codes,
                                                              const uint32_t* __restrict__ bits,
-                                                             const unsigned long long* __restrict__ group_start,
-                                                             uint32_t* __restrict__ words) {
+                                                             const unsigned long long* __restrict__ group_bits,
+                                                             int scanned, uint32_t* __restrict__ words,
+                                                             unsigned long long* __restrict__ total_bits) {
     __shared__ uint32_t C[kJpegTableCount * 256];
     __shared__ uint32_t W[kPackWords];
     __shared__ unsigned BB[kGroupBlocks];
@@ -364,11 +389,15 @@ __global__ __launch_bounds__(kThreads) void jpeg_pack_kernel(const int16_t* __re
     const int g0 = blockIdx.x * kGroupBlocks;
     const int b0 = g0 + wave * kBlocksPerWave;
     const WaveBlocks wb = load_blocks(coef, b0, n_blocks, lane);
-    const unsigned long long p0 = group_start[blockIdx.x];
-    const int off0 = (int)(p0 & 31);
     for (int i = threadIdx.x; i < kJpegTableCount * 256; i += kThreads) C[i] = codes[i];
     for (int i = threadIdx.x; i < kPackWords; i += kThreads) W[i] = 0u;
     if (threadIdx.x < kGroupBlocks) BB[threadIdx.x] = g0 + threadIdx.x < n_blocks ? bits[g0 + threadIdx.x] : 0u;
+    // the group's bit offset: the sum of the groups before it (up to a few thousand
+    // counts, each group adding its own; one workgroup scanning them all took 6 us
+    // beside the launch), or the scanned counts of a frame with more
+    const unsigned long long p0 =
+        scanned ? group_bits[blockIdx.x] : block_sum_before(group_bits, (long long)blockIdx.x);
+    const int off0 = (int)(p0 & 31);
     __syncthreads();
     int start = off0;                       // local bit position of the wave's first block
     for (int j = 0; j < wave * kBlocksPerWave; ++j) start += (int)BB[j];
@@ -404,6 +433,7 @@ __global__ __launch_bounds__(kThreads) void jpeg_pack_kernel(const int16_t* __re
     int end = off0;
     for (int j = 0; j < kGroupBlocks; ++j) end += (int)BB[j];
     if (last_group) {
+        if (threadIdx.x == 0) *total_bits = p0 + (unsigned)(end - off0);
         const int pad = (8 - (end - off0 + (int)(p0 & 7)) % 8) % 8;    // to a byte boundary of the stream
         if (pad && threadIdx.x == 0) lds_put(W, end, (1u << pad) - 1u, pad);
         end += pad;
@@ -421,7 +451,7 @@ __global__ __launch_bounds__(kThreads) void jpeg_pack_kernel(const int16_t* __re
     }
 }
 
-// ---- 6. byte stuffing ----
+// ---- 5. byte stuffing ----
 
 __device__ inline uint32_t word_byte(uint32_t w, int k) { return (w >> (24 - 8 * k)) & 0xFFu; }
 
@@ -440,54 +470,79 @@ __global__ __launch_bounds__(kThreads) void stuff_count_kernel(const uint32_t* _
                                                                const unsigned long long* __restrict__ total_bits,
                                                                unsigned long long* __restrict__ counts) {
     const unsigned long long n_bytes = (*total_bits + 7) / 8;
-    const unsigned long long c0 = (unsigned long long)blockIdx.x * kStuffChunk;
-    if (c0 >= n_bytes) {
-        if (threadIdx.x == 0) counts[blockIdx.x] = 0;
-        return;
+    for (unsigned long long chunk = blockIdx.x; chunk * kStuffChunk < n_bytes; chunk += gridDim.x) {
+        const unsigned long long k0 = chunk * kStuffChunk + threadIdx.x * kStuffPerThread;
+        uint32_t w[4];
+        const unsigned n = k0 < n_bytes ? load_stream(words, k0, n_bytes, w) : 0u;
+        unsigned long long all;
+        block_excl_scan(n, &all);
+        if (threadIdx.x == 0) counts[chunk] = all;
     }
-    const unsigned long long k0 = c0 + threadIdx.x * kStuffPerThread;
-    uint32_t w[4];
-    const unsigned n = k0 < n_bytes ? load_stream(words, k0, n_bytes, w) : 0u;
-    unsigned long long all;
-    block_excl_scan(n, &all);
-    if (threadIdx.x == 0) counts[blockIdx.x] = all;
 }
 
-// Copies the workgroup's chunk of stream with a 0x00 behind every 0xFF: the
-// bytes are placed in LDS first, then stored as aligned words (bytes at the ends).
-__global__ __launch_bounds__(kThreads) void stuff_write_kernel(const uint32_t* __restrict__ words,
+// Where the coded bytes go: pinned host memory as far as it reaches, chunks that
+// would pass its end to device memory at the same positions.
+struct StuffOut {
+    uint8_t* host;
+    unsigned long long host_cap;
+    uint8_t* dev;
+    // pinned: coded bits, 0xFF bytes, and the position from which the bytes are in dev
+    unsigned long long* totals;
+};
+
+// Copies each chunk of stream with a 0x00 behind every 0xFF: the bytes are placed
+// in LDS first, then stored as aligned words (bytes at the ends).  A chunk's
+// position is its start plus the 0xFF bytes of the chunks before it.  The stream's
+// words are left zero for the next frame.
+__global__ __launch_bounds__(kThreads) void stuff_write_kernel(uint32_t* __restrict__ words,
                                                                const unsigned long long* __restrict__ total_bits,
-                                                               const unsigned long long* __restrict__ ff_before,
-                                                               uint8_t* __restrict__ out) {
+                                                               const unsigned long long* __restrict__ counts,
+                                                               int scanned, StuffOut out) {
     __shared__ uint8_t L[2 * kStuffChunk];
-    const unsigned long long n_bytes = (*total_bits + 7) / 8;
-    const unsigned long long c0 = (unsigned long long)blockIdx.x * kStuffChunk;
-    if (c0 >= n_bytes) return;
-    const unsigned long long k0 = c0 + threadIdx.x * kStuffPerThread;
-    uint32_t w[4];
-    const unsigned n = k0 < n_bytes ? load_stream(words, k0, n_bytes, w) : 0u;
-    unsigned long long all;
-    unsigned pos = (unsigned)(threadIdx.x * kStuffPerThread + block_excl_scan(n, &all));
-    if (k0 < n_bytes)
-        for (int i = 0; i < kStuffPerThread; ++i) {
-            if (k0 + i >= n_bytes) break;
-            const uint32_t v = word_byte(w[i >> 2], i & 3);
-            L[pos++] = (uint8_t)v;
-            if (v == 0xFFu) L[pos++] = 0;
+    const unsigned long long bits = *total_bits, n_bytes = (bits + 7) / 8;
+    for (unsigned long long chunk = blockIdx.x; chunk * kStuffChunk < n_bytes; chunk += gridDim.x) {
+        const unsigned long long c0 = chunk * kStuffChunk;
+        const unsigned long long k0 = c0 + threadIdx.x * kStuffPerThread;
+        uint32_t w[4];
+        const unsigned n = k0 < n_bytes ? load_stream(words, k0, n_bytes, w) : 0u;
+        if (k0 < n_bytes) *reinterpret_cast<uint4*>(words + (k0 >> 2)) = make_uint4(0u, 0u, 0u, 0u);
+        const unsigned long long before =
+            scanned ? counts[chunk] : block_sum_before(counts, (long long)chunk);
+        unsigned long long all;
+        unsigned pos = (unsigned)(threadIdx.x * kStuffPerThread + block_excl_scan(n, &all));
+        if (k0 < n_bytes)
+            for (int i = 0; i < kStuffPerThread; ++i) {
+                if (k0 + i >= n_bytes) break;
+                const uint32_t v = word_byte(w[i >> 2], i & 3);
+                L[pos++] = (uint8_t)v;
+                if (v == 0xFFu) L[pos++] = 0;
+            }
+        __syncthreads();
+        const unsigned len = (unsigned)(std::min<unsigned long long>(kStuffChunk, n_bytes - c0) + all);
+        const unsigned long long at = c0 + before;
+        const bool fits = at + len <= out.host_cap;
+        if (threadIdx.x == 0) {
+            const bool last = n_bytes - c0 <= kStuffChunk;
+            if (last) {
+                out.totals[0] = bits;
+                out.totals[1] = before + all;
+            }
+            if (fits ? last : at <= out.host_cap) out.totals[2] = fits ? at + len : at;
         }
-    __syncthreads();
-    const unsigned len = (unsigned)(std::min<unsigned long long>(kStuffChunk, n_bytes - c0) + all);
-    uint8_t* dst = out + c0 + ff_before[blockIdx.x];
-    const unsigned head = std::min(len, (unsigned)((4 - ((uintptr_t)dst & 3)) & 3));
-    if (threadIdx.x < head) dst[threadIdx.x] = L[threadIdx.x];
-    const unsigned n4 = (len - head) / 4;
-    uint32_t* d4 = reinterpret_cast<uint32_t*>(dst + head);
-    for (unsigned i = threadIdx.x; i < n4; i += kThreads) {
-        const unsigned q = head + 4 * i;
-        d4[i] = (uint32_t)L[q] | ((uint32_t)L[q + 1] << 8) | ((uint32_t)L[q + 2] << 16) | ((uint32_t)L[q + 3] << 24);
+        uint8_t* dst = (fits ? out.host : out.dev) + at;
+        const unsigned head = std::min(len, (unsigned)((4 - ((uintptr_t)dst & 3)) & 3));
+        if (threadIdx.x < head) dst[threadIdx.x] = L[threadIdx.x];
+        const unsigned n4 = (len - head) / 4;
+        uint32_t* d4 = reinterpret_cast<uint32_t*>(dst + head);
+        for (unsigned i = threadIdx.x; i < n4; i += kThreads) {
+            const unsigned q = head + 4 * i;
+            d4[i] = (uint32_t)L[q] | ((uint32_t)L[q + 1] << 8) | ((uint32_t)L[q + 2] << 16) |
+                    ((uint32_t)L[q + 3] << 24);
+        }
+        const unsigned t0 = head + 4 * n4;
+        if (threadIdx.x < len - t0) dst[t0 + threadIdx.x] = L[t0 + threadIdx.x];
+        __syncthreads();                        // the bytes in L before the next chunk's
     }
-    const unsigned t0 = head + 4 * n4;
-    if (threadIdx.x < len - t0) dst[t0 + threadIdx.x] = L[t0 + threadIdx.x];
 }
 
 __global__ void fill_u32_kernel(uint32_t* __restrict__ p, long long n) {
@@ -501,14 +556,13 @@ struct JpegWork {
     JpegTables* tables = nullptr;        // device
     uint32_t* codes = nullptr;           // device [4][256]
     uint32_t* hist = nullptr;            // device [kHistCopies][4][256], zero between frames
-    uint32_t* hist_sum = nullptr;        // device [4][256]
     uint32_t* lens = nullptr;            // device [4][256] code lengths, bytes
-    unsigned long long* totals = nullptr;  // device [2]: bit total, 0xFF total
+    unsigned long long* total_bits = nullptr;   // device
     uint32_t* host_hist = nullptr;       // pinned [4][256]
-    unsigned long long* host_totals = nullptr;  // pinned [2]
+    unsigned long long* host_totals = nullptr;  // pinned [3]: coded bits, 0xFF bytes, bytes in host_out
     uint32_t* host_codes = nullptr;      // pinned [4][256]
     uint8_t* host_lens = nullptr;        // pinned [4][256]
-    uint8_t* host_out = nullptr;         // pinned staging of the coded bytes
+    uint8_t* host_out = nullptr;         // pinned: the coded bytes, written by the device
     size_t host_out_cap = 0;
     JpegTables host_tables{};
     int quality = -1;
@@ -538,6 +592,20 @@ hipError_t grow(JpegWork* w, int i, size_t bytes) {
     }
     hipError_t e = hipMalloc(&w->buf[i], bytes);
     if (e == hipSuccess) w->cap[i] = bytes;
+    ++w->generation;
+    return e;
+}
+
+// The pinned output buffer at `bytes` or more, keeping its first `keep` bytes.
+hipError_t grow_host(JpegWork* w, size_t bytes, size_t keep) {
+    if (bytes <= w->host_out_cap) return hipSuccess;
+    void* p = nullptr;
+    hipError_t e = hipHostMalloc(&p, bytes);
+    if (e != hipSuccess) return e;
+    if (keep) memcpy(p, w->host_out, keep);
+    if (w->host_out) e = hipHostFree(w->host_out);
+    w->host_out = static_cast<uint8_t*>(p);
+    w->host_out_cap = bytes;
     ++w->generation;
     return e;
 }
@@ -578,13 +646,12 @@ void jpeg_work_destroy(JpegWork* w) {
     if (w->tables) hipFree(w->tables);
     if (w->codes) hipFree(w->codes);
     if (w->hist) hipFree(w->hist);
-    if (w->hist_sum) hipFree(w->hist_sum);
     if (w->lens) hipFree(w->lens);
     if (w->host_lens) hipHostFree(w->host_lens);
     if (w->seg_a) hipGraphExecDestroy(w->seg_a);
     if (w->seg_b) hipGraphExecDestroy(w->seg_b);
     if (w->capture) hipStreamDestroy(w->capture);
-    if (w->totals) hipFree(w->totals);
+    if (w->total_bits) hipFree(w->total_bits);
     if (w->host_hist) hipHostFree(w->host_hist);
     if (w->host_totals) hipHostFree(w->host_totals);
     if (w->host_codes) hipHostFree(w->host_codes);
@@ -618,15 +685,14 @@ int jpeg_encode(JpegWork* w, const uint8_t* rgba8, int width, int height, int qu
         JPEG_TRY(hipMalloc(&w->tables, sizeof(JpegTables)));
         JPEG_TRY(hipMalloc(&w->codes, kJpegTableCount * 256 * sizeof(uint32_t)));
         JPEG_TRY(hipMalloc(&w->hist, kHistCopies * kJpegTableCount * 256 * sizeof(uint32_t)));
-        JPEG_TRY(hipMalloc(&w->hist_sum, kJpegTableCount * 256 * sizeof(uint32_t)));
         JPEG_TRY(hipMalloc(&w->lens, kJpegTableCount * 256));
         JPEG_TRY(hipHostMalloc(reinterpret_cast<void**>(&w->host_lens), kJpegTableCount * 256));
         fill_u32_kernel<<<64, 256, 0, s>>>(w->hist, kHistCopies * kJpegTableCount * 256);
         JPEG_TRY(hipGetLastError());
-        JPEG_TRY(hipMalloc(&w->totals, 2 * sizeof(unsigned long long)));
+        JPEG_TRY(hipMalloc(&w->total_bits, sizeof(unsigned long long)));
         JPEG_TRY(hipHostMalloc(reinterpret_cast<void**>(&w->host_hist), kJpegTableCount * 256 * sizeof(uint32_t)));
         JPEG_TRY(hipHostMalloc(reinterpret_cast<void**>(&w->host_codes), kJpegTableCount * 256 * sizeof(uint32_t)));
-        JPEG_TRY(hipHostMalloc(reinterpret_cast<void**>(&w->host_totals), 2 * sizeof(unsigned long long)));
+        JPEG_TRY(hipHostMalloc(reinterpret_cast<void**>(&w->host_totals), 3 * sizeof(unsigned long long)));
         JPEG_TRY(hipStreamCreateWithFlags(&w->capture, hipStreamNonBlocking));
     }
     if (w->quality != quality) {
@@ -643,9 +709,17 @@ int jpeg_encode(JpegWork* w, const uint8_t* rgba8, int width, int height, int qu
     JPEG_TRY(grow(w, B_COEF, (size_t)n_blocks * 64 * sizeof(int16_t)));
     JPEG_TRY(grow(w, B_BITS, (size_t)n_blocks * sizeof(uint32_t)));
     JPEG_TRY(grow(w, B_GROUP, (size_t)groups * sizeof(unsigned long long)));
+    const size_t words_before = w->cap[B_WORDS];
     JPEG_TRY(grow(w, B_WORDS, (size_t)stuff_groups * kStuffChunk));
+    if (w->cap[B_WORDS] != words_before) {       // zero between frames
+        fill_u32_kernel<<<1024, 256, 0, s>>>(static_cast<uint32_t*>(w->buf[B_WORDS]), (long long)(w->cap[B_WORDS] / 4));
+        JPEG_TRY(hipGetLastError());
+    }
     JPEG_TRY(grow(w, B_STUFF, (size_t)stuff_groups * sizeof(unsigned long long)));
     JPEG_TRY(grow(w, B_OUT, (size_t)stuff_groups * kStuffChunk * 2));
+    // a byte per pixel holds the stream of all but noise; one that passes it comes
+    // through device memory, and the pinned buffer grows for the next
+    JPEG_TRY(grow_host(w, std::max<size_t>((size_t)width * height, 64 << 10), 0));
     auto* coef = static_cast<int16_t*>(w->buf[B_COEF]);
     auto* bits = static_cast<uint32_t*>(w->buf[B_BITS]);
     auto* group = static_cast<unsigned long long*>(w->buf[B_GROUP]);
@@ -659,12 +733,8 @@ int jpeg_encode(JpegWork* w, const uint8_t* rgba8, int width, int height, int qu
     JPEG_TRY(replay(w, &w->seg_a, same_a, s, [&](hipStream_t st) {
         jpeg_coef_kernel<<<coef_groups, kThreads, 0, st>>>(rgba8, width, height, mcu_cols, n_mcu, w->tables, coef);
         jpeg_hist_kernel<<<(unsigned)groups, kThreads, 0, st>>>(coef, n_blocks, w->hist);
-        jpeg_hist_reduce_kernel<<<kJpegTableCount * 256 / kThreads, kThreads, 0, st>>>(w->hist, w->hist_sum);
-        hipError_t e = hipGetLastError();
-        if (e == hipSuccess)
-            e = hipMemcpyAsync(w->host_hist, w->hist_sum, kJpegTableCount * 256 * sizeof(uint32_t),
-                               hipMemcpyDeviceToHost, st);
-        return e;
+        jpeg_hist_reduce_kernel<<<kJpegTableCount * 256 / kThreads, kThreads, 0, st>>>(w->hist, w->host_hist);
+        return hipGetLastError();
     }));
     w->a_rgba = rgba8, w->a_width = width, w->a_height = height, w->a_gen = w->generation;
     JPEG_TRY(hipStreamSynchronize(s));
@@ -679,23 +749,23 @@ int jpeg_encode(JpegWork* w, const uint8_t* rgba8, int width, int height, int qu
         memcpy(w->host_lens + k * 256, len, 256);
     }
 
-    // 3-6: bits, offsets, packing, stuffing (a graph per buffer set)
+    // 3-5: bits, packing, stuffing (a graph per buffer set)
     const bool same_b = w->b_blocks == n_blocks && w->b_gen == w->generation;
+    // offsets by summing what comes before, or scanned where that would be long
+    const int scan_groups = groups > kMaxSummedGroups, scan_chunks = stuff_groups > kMaxSummedChunks;
+    const unsigned stuff_grid = (unsigned)std::min<long long>(stuff_groups, kStuffGrid);
     JPEG_TRY(replay(w, &w->seg_b, same_b, s, [&](hipStream_t st) {
-        hipError_t e = hipMemcpyAsync(w->codes, w->host_codes, kJpegTableCount * 256 * sizeof(uint32_t),
-                                      hipMemcpyHostToDevice, st);
-        if (e == hipSuccess) e = hipMemcpyAsync(w->lens, w->host_lens, kJpegTableCount * 256, hipMemcpyHostToDevice, st);
-        if (e != hipSuccess) return e;
+        jpeg_tables_kernel<<<1, kThreads, 0, st>>>(w->host_codes, reinterpret_cast<const uint32_t*>(w->host_lens),
+                                                   w->codes, w->lens);
         jpeg_bits_kernel<<<(unsigned)groups, kThreads, 0, st>>>(coef, n_blocks, w->lens, bits, group);
-        scan_top_kernel<<<1, kThreads, 0, st>>>(group, groups, w->totals, words);
-        jpeg_pack_kernel<<<(unsigned)groups, kThreads, 0, st>>>(coef, n_blocks, w->codes, bits, group, words);
-        stuff_count_kernel<<<(unsigned)stuff_groups, kThreads, 0, st>>>(words, w->totals, ffcnt);
-        scan_top_kernel<<<1, kThreads, 0, st>>>(ffcnt, stuff_groups, w->totals + 1, nullptr);
-        stuff_write_kernel<<<(unsigned)stuff_groups, kThreads, 0, st>>>(words, w->totals, ffcnt, dst);
-        e = hipGetLastError();
-        if (e == hipSuccess)
-            e = hipMemcpyAsync(w->host_totals, w->totals, 2 * sizeof(unsigned long long), hipMemcpyDeviceToHost, st);
-        return e;
+        if (scan_groups) scan_top_kernel<<<1, kThreads, 0, st>>>(group, groups, nullptr);
+        jpeg_pack_kernel<<<(unsigned)groups, kThreads, 0, st>>>(coef, n_blocks, w->codes, bits, group, scan_groups,
+                                                                words, w->total_bits);
+        stuff_count_kernel<<<stuff_grid, kThreads, 0, st>>>(words, w->total_bits, ffcnt);
+        if (scan_chunks) scan_top_kernel<<<1, kThreads, 0, st>>>(ffcnt, stuff_groups, w->total_bits);
+        stuff_write_kernel<<<stuff_grid, kThreads, 0, st>>>(
+            words, w->total_bits, ffcnt, scan_chunks, StuffOut{w->host_out, w->host_out_cap, dst, w->host_totals});
+        return hipGetLastError();
     }));
     w->b_blocks = n_blocks, w->b_gen = w->generation;
     JPEG_TRY(hipStreamSynchronize(s));
@@ -708,15 +778,12 @@ int jpeg_encode(JpegWork* w, const uint8_t* rgba8, int width, int height, int qu
     if (!out || capacity < need)
         return fail(ISAAC_ERR_INVALID_ARGUMENT, "output capacity below the stream size (written to out_size)",
                     hipSuccess);
-    if (coded > w->host_out_cap) {
-        if (w->host_out) JPEG_TRY(hipHostFree(w->host_out));
-        w->host_out = nullptr;
-        w->host_out_cap = 0;
-        JPEG_TRY(hipHostMalloc(reinterpret_cast<void**>(&w->host_out), coded));
-        w->host_out_cap = coded;
+    const size_t in_host = (size_t)w->host_totals[2];
+    if (in_host < coded) {
+        JPEG_TRY(grow_host(w, coded, in_host));
+        JPEG_TRY(hipMemcpyAsync(w->host_out + in_host, dst + in_host, coded - in_host, hipMemcpyDeviceToHost, s));
+        JPEG_TRY(hipStreamSynchronize(s));
     }
-    JPEG_TRY(hipMemcpyAsync(w->host_out, dst, coded, hipMemcpyDeviceToHost, s));
-    JPEG_TRY(hipStreamSynchronize(s));
     memcpy(out, hdr, hdr_len);
     memcpy(out + hdr_len, w->host_out, coded);
     out[hdr_len + coded] = 0xFF;
