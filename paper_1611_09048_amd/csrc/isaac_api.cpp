@@ -318,15 +318,7 @@ isaac_status new_tf_slot(isaac_context* ctx, const float* table, int32_t* handle
         }
     if (slot < 0)
         return set_err(ctx, ISAAC_ERR_OUT_OF_MEMORY, "all %d transfer tables are live; release some", ctx->tf_capacity);
-    // device layout: per entry the value and the difference to the next entry (FP32, as the lookup uses it;
-    // the last entry's difference is 0, and the lookup reads it at the top of the range)
-    float rows[kTfRows * 4];
-    for (int j = 0; j < kTfEntries; ++j)
-        for (int c = 0; c < 4; ++c) {
-            rows[8 * j + c] = table[4 * j + c];
-            rows[8 * j + 4 + c] = j + 1 < kTfEntries ? table[4 * (j + 1) + c] - table[4 * j + c] : 0.0f;
-        }
-    HIP_TRY(ctx, hipMemcpy(ctx->tf_pool + (size_t)slot * kTfRows * 4, rows, kTfRows * 4 * sizeof(float),
+    HIP_TRY(ctx, hipMemcpy(ctx->tf_pool + (size_t)slot * kTfEntries * 4, table, kTfEntries * 4 * sizeof(float),
                            hipMemcpyHostToDevice));
     ctx->tf_slots[slot] = TfSlot();
     ctx->tf_slots[slot].live = true;
@@ -1253,12 +1245,12 @@ isaac_status isaac_init(const isaac_init_desc* desc, isaac_context** out) {
         if (e == hipSuccess) e = hipEventCreateWithFlags(&r.done, hipEventDisableTiming);
         if (e != hipSuccess) return fail("staging ring", e);
     }
-    e = hipMalloc((void**)&ctx->tf_pool, (size_t)kTfSlots * kTfRows * 4 * sizeof(float));
+    e = hipMalloc((void**)&ctx->tf_pool, (size_t)kTfSlots * kTfEntries * 4 * sizeof(float));
     if (e != hipSuccess) return fail("transfer table pool", e);
     ctx->tf_capacity = kTfSlots;
     ctx->tf_slots.resize(kTfSlots);
     // slot 0: the all-zero table of sources without a transfer function
-    e = hipMemset(ctx->tf_pool, 0, kTfRows * 4 * sizeof(float));
+    e = hipMemset(ctx->tf_pool, 0, kTfEntries * 4 * sizeof(float));
     if (e != hipSuccess) return fail("hipMemset", e);
     ctx->tf_slots[0].live = true;
     e = hipDeviceSynchronize();

@@ -1039,9 +1039,11 @@ __device__ __forceinline__ void group_scan(int lane, float& c0, float& c1, float
 // past the row's last kept point.
 // The lane index, opaque to the optimizer: masks and permute addresses made from
 // it inside a loop are recomputed there (one instruction each) instead of held in
-// registers through it.
-__device__ __forceinline__ int fresh(int lane) {
-    asm volatile("" : "+v"(lane));
+// registers through it.  k0 (the loop's) keeps it in the loop; volatile would too, but
+// counts as a write to memory and keeps the job's fields from being read once
+// before the loop.
+__device__ __forceinline__ int fresh(int lane, int k0) {
+    asm("" : "+v"(lane) : "v"(k0));
     return lane;
 }
 
@@ -1053,7 +1055,7 @@ __device__ __forceinline__ bool row_composite(const DevJob& J, const RaySetup& R
     const float n0 = fmaf(T, c0, acc.C0), n1 = fmaf(T, c1, acc.C1), n2 = fmaf(T, c2, acc.C2), na = fmaf(T, a, acc.A);
     const unsigned long long m = __builtin_amdgcn_ballot_w64(na >= J.ert) & __builtin_amdgcn_ballot_w64(valid);
     constexpr unsigned long long kGroupMask = G == 64 ? ~0ull : ((1ull << (G & 63)) - 1ull);
-    const int first = fresh(lane) & ~(G - 1);
+    const int first = fresh(lane, k0) & ~(G - 1);
     const unsigned long long bits = (m >> first) & kGroupMask;
     const bool stop = bits != 0;
     // the first terminating point, else the row's last kept one (k0 < R.ke, so
@@ -1078,7 +1080,7 @@ __device__ __forceinline__ bool row_composite(const DevJob& J, const RaySetup& R
 template <int INTERP, int G, int SIG, bool PS>
 __device__ __forceinline__ bool lanes_row(const DevJob& J, const float4* __restrict__ s_tf, const RaySetup& R,
                                           int lane, int k0, RayAccum& acc) {
-    const int k = k0 + (fresh(lane) & (G - 1));
+    const int k = k0 + (fresh(lane, k0) & (G - 1));
     const bool valid = k < R.ke;
     float E[3], S;
     point<INTERP, SIG, PS>(J, s_tf, R, valid ? k : R.ke - 1, E, S);
@@ -1302,6 +1304,38 @@ __device__ __forceinline__ bool pixel_of(const DevJob& J, int t, int lane, int w
     return px <= J.cull[2] && py <= J.cull[3];
 }
 
+// Staging of a workgroup's transfer tables in LDS, a value per thread and source:
+// the first three loaded to registers ahead, any others when they are stored.
+struct StagedTables {
+    float4 t0, t1, t2;
+};
+
+__device__ __forceinline__ float4 table_entry(const DevJob& J, const float4* __restrict__ tf_pool, int s) {
+    static_assert(kBlockThreads == kTfEntries, "one table entry per thread");
+    return tf_pool[(size_t)J.src[s].tf_slot * kTfEntries + threadIdx.x];
+}
+
+__device__ __forceinline__ StagedTables load_tables(const DevJob& J, const float4* __restrict__ tf_pool) {
+    const float4 zero = make_float4(0.f, 0.f, 0.f, 0.f);
+    StagedTables t;
+    t.t0 = J.n_src > 0 ? table_entry(J, tf_pool, 0) : zero;
+    t.t1 = J.n_src > 1 ? table_entry(J, tf_pool, 1) : zero;
+    t.t2 = J.n_src > 2 ? table_entry(J, tf_pool, 2) : zero;
+    return t;
+}
+
+__device__ __forceinline__ void store_tables(const DevJob& J, const float4* __restrict__ tf_pool,
+                                             const StagedTables& t, float4* __restrict__ s_tf) {
+    auto put = [&](int s, const float4& v) {
+        s_tf[s * kTfLds + threadIdx.x] = v;
+        if (threadIdx.x == kTfEntries - 1) s_tf[s * kTfLds + kTfEntries] = v;   // the last entry's copy
+    };
+    if (J.n_src > 0) put(0, t.t0);
+    if (J.n_src > 1) put(1, t.t1);
+    if (J.n_src > 2) put(2, t.t2);
+    for (int s = 3; s < J.n_src; ++s) put(s, table_entry(J, tf_pool, s));
+}
+
 // One workgroup per tile, for one job or the tiles of many.  (Batches once ran a
 // resident set of workgroups over a tile queue, to stage a job's tables once for
 // many tiles: 1303 against 1256 us a call for 64 sub-volumes, 533 against 439 us for
@@ -1323,6 +1357,14 @@ void raycast_kernel(const DevJob* __restrict__ jobs, const float4* __restrict__ 
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const int tile = tile0 + (int)blockIdx.x;
     const DevJob& J = jobs[__builtin_amdgcn_readfirstlane(find_job(jobs, n_jobs, tile))];
+    // Loops over adjacent values: the tables travel while the ray record does, whether a
+    // ray of the tile meets the box or not, so a workgroup waits for memory once before
+    // its rows, not for the record, then for the tables (a wave lives 8.6 us on the
+    // average; 8 bricks at 1920 x 1080 526 -> 517 us a call).  The longer loops over
+    // sources in place (272 against 274 us) stage for the tiles that need them.
+    constexpr bool kEarly = Il<SIGK>::n > 0;
+    StagedTables tab;
+    if constexpr (kEarly) tab = load_tables(J, tf_pool);
     // tiles cover the box's screen rectangle only (the fill kernel clears the rest)
     int px = 0, py = 0;
     const bool in_image = pixel_of<G>(J, tile - J.tile_begin, lane, wave, px, py);
@@ -1350,13 +1392,11 @@ void raycast_kernel(const DevJob* __restrict__ jobs, const float4* __restrict__ 
     }
     if (J.out_depth && in_image && (lane & (G - 1)) == 0)
         J.out_depth[(size_t)py * J.width + px] = hit ? R.t_first : __builtin_inff();
-    // tiles no ray of which meets the box skip the transfer tables
-    if (__syncthreads_or(hit)) {
-        const int n = J.n_src * kTfLds;
-        for (int i = threadIdx.x; i < n; i += kBlockThreads) {
-            const int s = i / kTfLds, e = min(i % kTfLds, kTfEntries - 1);
-            s_tf[i] = tf_pool[(size_t)J.src[s].tf_slot * kTfRows + 2 * e];
-        }
+    if constexpr (kEarly) {
+        store_tables(J, tf_pool, tab, s_tf);
+        __syncthreads();
+    } else if (__syncthreads_or(hit)) {
+        store_tables(J, tf_pool, load_tables(J, tf_pool), s_tf);
         __syncthreads();
     }
     float4 c = make_float4(0.f, 0.f, 0.f, 0.f);
@@ -1460,12 +1500,8 @@ void raycast_pool_kernel(const DevJob* __restrict__ jobs, const float4* __restri
                          const RayRec* __restrict__ rays, int* __restrict__ counters) {
     extern __shared__ float4 s_tf[];
     const DevJob& J = jobs[0];
-    {
-        const int n = J.n_src * kTfLds;
-        for (int i = (int)threadIdx.x; i < n; i += kBlockThreads)
-            s_tf[i] = tf_pool[(size_t)J.src[i / kTfLds].tf_slot * kTfRows + 2 * min(i % kTfLds, kTfEntries - 1)];
-        __syncthreads();
-    }
+    store_tables(J, tf_pool, load_tables(J, tf_pool), s_tf);
+    __syncthreads();
     const int n_rays = __builtin_amdgcn_readfirstlane(counters[0]);   // the setup kernel's count
     const int lane = (int)(threadIdx.x & 63);
     const int leader = lane & ~(G - 1);
