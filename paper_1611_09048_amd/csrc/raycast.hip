@@ -522,6 +522,21 @@ __device__ __forceinline__ void fetch_kind(const DevSource& S, const int (&off)[
     }
 }
 
+// The 8 corners of an FP32 scalar whose x neighbours are 4 bytes apart, in 4 loads.
+__device__ __forceinline__ void fetch_f32_pairs(const DevSource& S, const int (&off)[8], float (&v)[8][4]) {
+    typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
+    const __amdgpu_buffer_rsrc_t r = make_rsrc(S.base[0], S.num_records[0]);
+    const int o = S.comp_off[0];
+#pragma unroll
+    for (int i = 0; i < 8; i += 2) {
+        const u32x2 x = __builtin_amdgcn_raw_buffer_load_b64(r, off[i] + o, 0, 0);
+        v[i][0] = __builtin_bit_cast(float, x.x);
+        v[i + 1][0] = __builtin_bit_cast(float, x.y);
+#pragma unroll
+        for (int c = 1; c < 4; ++c) v[i][c] = v[i + 1][c] = 0.f;
+    }
+}
+
 // Sources of 16-bit values whose x neighbours are adjacent (2 D bytes apart): the
 // D values of voxels x and x + 1 are 4 D consecutive bytes at an even address, and
 // one aligned load of 8 (D = 1) or 16 bytes (D = 3) holds them, 4 loads for the 8
@@ -859,7 +874,13 @@ __device__ __forceinline__ void point(const DevJob& J, const float4* __restrict_
             int off[NV];
             if (NS > 0) {
                 corner_offsets<INTERP, CL>(J.src[0], dims, i0, off);
-                fetch_kind<K0, NV>(J.src[0], off, vals[0]);
+                // an FP32 scalar whose x neighbours are adjacent: both in one load
+                bool pairs = false;
+                if constexpr (SIG == SIG_PIC3_F32 && INTERP != 0) {
+                    pairs = J.src[0].stride[0] == 4;
+                    if (pairs) fetch_f32_pairs(J.src[0], off, vals[0]);
+                }
+                if (!pairs) fetch_kind<K0, NV>(J.src[0], off, vals[0]);
             }
             if (NS > 1) {
                 corner_offsets<INTERP, CL>(J.src[1], dims, i0, off);
