@@ -530,8 +530,9 @@ __device__ __forceinline__ void fetch_f32_pairs(const DevSource& S, const int (&
 #pragma unroll
     for (int i = 0; i < 8; i += 2) {
         const u32x2 x = __builtin_amdgcn_raw_buffer_load_b64(r, off[i] + o, 0, 0);
-        v[i][0] = __builtin_bit_cast(float, x.x);
-        v[i + 1][0] = __builtin_bit_cast(float, x.y);
+        const unsigned lo = x.x, hi = x.y;       // (bit_cast of a vector's element takes its first)
+        v[i][0] = __builtin_bit_cast(float, lo);
+        v[i + 1][0] = __builtin_bit_cast(float, hi);
 #pragma unroll
         for (int c = 1; c < 4; ++c) v[i][c] = v[i + 1][c] = 0.f;
     }
