@@ -133,7 +133,9 @@ typedef struct {
     const void* comp[4];              /* device; BORROWED, never written */
     int64_t stride[3];                /* bytes along x, y, z */
     int guard;                        /* guard layers present in memory (0: border clamped under interpolation) */
-    int persistent;                   /* 0: the library copies the field after update() into its own buffer */
+    int persistent;                   /* 0: the field may be reused after the next update() or the call: the library
+                                         copies it after update() into its own buffer (or reads it in place in a call
+                                         that waits for its images and makes no later update()) */
     const char* functor_chain;        /* e.g. "mul(2,3,4) | add(1) | length"; NULL or "": identity */
     float weight;                     /* in [0,1]: scales the source's opacity when sources are combined */
     int enabled;                      /* 0: never read */
