@@ -4,11 +4,11 @@
 // server (Sec. 3.6).  Here every data-parallel step runs on the GPU:
 //   1. coef:   one wave per MCU (8x8 pixels, three components): colour
 //              conversion, separable integer DCT through LDS, quantisation,
-//              zigzag; 64 int16 per block, blocks in scan order (Y, Cb, Cr per MCU);
-//   2. hist:   one lane per coefficient, 4 blocks per wave with their loads in
-//              flight together: each block's symbols come from a ballot of the
-//              nonzero lanes (run = distance to the highest nonzero lane below),
-//              counted per table in LDS;
+//              zigzag; 64 int16 per block, blocks in scan order (Y, Cb, Cr per
+//              MCU); one lane per coefficient, each block's symbols come from a
+//              ballot of the nonzero lanes (run = distance to the highest nonzero
+//              lane below), counted per table in LDS;
+//   2. counts: the copies of the symbol counts summed;
 //   (host)     Huffman code lengths and codes per table (Annex K.2);
 //   3. bits:   the same symbols priced with the codes: bits per block and per
 //              workgroup (32 blocks);
@@ -169,89 +169,123 @@ __device__ inline unsigned long long block_excl_scan(unsigned long long v, unsig
     return before + incl - v;
 }
 
-// ---- 1. coefficients ----
+// ---- 1. coefficients and symbol counts ----
 
+// Colour of one pixel as three level-shifted samples.
+__device__ inline void samples_of(uint32_t px, int (&s)[3]) {
+    const int R = px & 255, G = (px >> 8) & 255, B = (px >> 16) & 255;
+    const int Y = (19595 * R + 38470 * G + 7471 * B + 32768) >> 16;
+    const int Cb = ((-11059 * R - 21709 * G + 32768 * B + 32768) >> 16) + 128;
+    const int Cr = ((32768 * R - 27439 * G - 5329 * B + 32768) >> 16) + 128;
+    s[0] = min(max(Y, 0), 255) - 128;
+    s[1] = min(max(Cb, 0), 255) - 128;
+    s[2] = min(max(Cr, 0), 255) - 128;
+}
+
+// |f| <= 1024 for 8-bit samples, so the dividend stays below 2^12 and the
+// reciprocal product below 2^32 (24-bit operands).
+__device__ inline int quantise(int f, int q, unsigned qinv) {
+    const unsigned a = (unsigned)((f < 0 ? -f : f) + (q >> 1));
+    const int mag = (int)(__umul24(a, qinv) >> 20);
+    return f < 0 ? -mag : mag;
+}
+
+// LDS written by this wave before is visible to it after: a wave's LDS accesses are
+// in order, so this only keeps the compiler from moving them (no barrier across
+// the workgroup, whose waves work on MCUs of their own).
+__device__ inline void wave_lds_fence() {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
+// Bound by each wave's chain of LDS passes, not by memory (4 bytes read and 6
+// written per pixel).  The symbols are counted here, while a block's coefficients
+// are in registers: a pass of its own read them back (9 us of 22 for both at
+// 1920 x 1080).  The DC of the MCU before the workgroup's first is worked out again
+// from its pixels (row and column 0 of the transform only).
 __global__ __launch_bounds__(kThreads) void jpeg_coef_kernel(const uint8_t* __restrict__ rgba, int width, int height,
                                                              int mcu_cols, int n_mcu,
                                                              const JpegTables* __restrict__ tab,
-                                                             int16_t* __restrict__ coef) {
+                                                             int16_t* __restrict__ coef, uint32_t* __restrict__ hist) {
     __shared__ int S[kWaves][3][64];
     __shared__ int T[kWaves][3][64];
     __shared__ JpegTables TB;
+    __shared__ uint32_t H[kJpegTableCount * 256];
+    __shared__ int DC[1 + kWaves * kMcuPerWave][3];       // of the MCU before the workgroup's first, then its own
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
     const int r = lane >> 3, c = lane & 7;
-    const int m0 = (blockIdx.x * kWaves + wave) * kMcuPerWave;
-    for (int i = threadIdx.x; i < (int)(sizeof(JpegTables) / 4); i += kThreads)
-        reinterpret_cast<int32_t*>(&TB)[i] = reinterpret_cast<const int32_t*>(tab)[i];
-    // this lane's pixel of each of the wave's MCUs, all loads in flight together
-    // (an MCU beyond the frame reads the last one's pixel and is not stored)
-    uint32_t px[kMcuPerWave];
-    for (int i = 0; i < kMcuPerWave; ++i) {
-        const int mcu = min(m0 + i, n_mcu - 1);
+    const int g0 = blockIdx.x * kWaves * kMcuPerWave, m0 = g0 + wave * kMcuPerWave;
+    auto pixel = [&](int mcu) {
         const int by = mcu / mcu_cols, bx = mcu - by * mcu_cols;
         const int x = min(bx * 8 + c, width - 1), y = min(by * 8 + r, height - 1);
-        px[i] = *reinterpret_cast<const uint32_t*>(rgba + ((size_t)y * width + x) * 4);
-    }
+        return *reinterpret_cast<const uint32_t*>(rgba + ((size_t)y * width + x) * 4);
+    };
+    // this lane's pixel of each of the wave's MCUs, all loads in flight together
+    // (an MCU beyond the frame reads the last one's pixel and is not stored)
+    uint32_t px[kMcuPerWave], before = 0;
+    for (int i = 0; i < kMcuPerWave; ++i) px[i] = pixel(min(m0 + i, n_mcu - 1));
+    if (wave == 0 && g0 > 0) before = pixel(g0 - 1);
+    for (int i = threadIdx.x; i < (int)(sizeof(JpegTables) / 4); i += kThreads)
+        reinterpret_cast<int32_t*>(&TB)[i] = reinterpret_cast<const int32_t*>(tab)[i];
+    for (int i = threadIdx.x; i < kJpegTableCount * 256; i += kThreads) H[i] = 0;
     __syncthreads();
     // per lane: the row pass output (y = r, u = c) needs M[c][*], the column pass (v = r, u = c) M[r][*]
     int mu[8], mv[8];
     for (int i = 0; i < 8; ++i) mu[i] = TB.dct[c * 8 + i], mv[i] = TB.dct[r * 8 + i];
     const int q0 = TB.quant[0][lane], q1 = TB.quant[1][lane], zz = TB.zz[lane];
     const unsigned r0 = TB.qinv[0][lane], r1 = TB.qinv[1][lane];
+    if (wave == 0) {
+        int s[3] = {0, 0, 0};
+        samples_of(before, s);
+        const int m = TB.dct[0];                           // M[0][x] is the same for every x
+        for (int k = 0; k < 3; ++k) {
+            int v = s[k];
+            for (int d = 1; d < 8; d <<= 1) v += __shfl_xor(v, d);
+            v = (m * v + 512) >> 10;                       // row r, u = 0
+            for (int d = 8; d < 64; d <<= 1) v += __shfl_xor(v, d);
+            const int f = (m * v + 8192) >> 14;
+            if (lane == 0) DC[0][k] = g0 > 0 ? quantise(f, k ? q1 : q0, k ? r1 : r0) : 0;
+        }
+    }
     for (int i = 0; i < kMcuPerWave; ++i) {
         const int mcu = m0 + i;
-        const bool live = mcu < n_mcu;
-        if (live) {
-            const int R = px[i] & 255, G = (px[i] >> 8) & 255, B = (px[i] >> 16) & 255;
-            const int Y = (19595 * R + 38470 * G + 7471 * B + 32768) >> 16;
-            const int Cb = ((-11059 * R - 21709 * G + 32768 * B + 32768) >> 16) + 128;
-            const int Cr = ((32768 * R - 27439 * G - 5329 * B + 32768) >> 16) + 128;
-            S[wave][0][lane] = min(max(Y, 0), 255) - 128;
-            S[wave][1][lane] = min(max(Cb, 0), 255) - 128;
-            S[wave][2][lane] = min(max(Cr, 0), 255) - 128;
+        if (mcu >= n_mcu) break;
+        int s[3];
+        samples_of(px[i], s);
+        for (int k = 0; k < 3; ++k) S[wave][k][lane] = s[k];
+        wave_lds_fence();
+        for (int k = 0; k < 3; ++k) {
+            int acc = 0;
+            for (int x = 0; x < 8; ++x) acc += __mul24(mu[x], S[wave][k][r * 8 + x]);   // |M| < 2^11, |s| <= 2^7
+            T[wave][k][lane] = (acc + 512) >> 10;          // two fractional bits kept
         }
-        __syncthreads();
-        if (live)
-            for (int k = 0; k < 3; ++k) {
-                int acc = 0;
-                for (int x = 0; x < 8; ++x) acc += __mul24(mu[x], S[wave][k][r * 8 + x]);   // |M| < 2^11, |s| <= 2^7
-                T[wave][k][lane] = (acc + 512) >> 10;          // two fractional bits kept
+        wave_lds_fence();
+        for (int k = 0; k < 3; ++k) {
+            int acc = 0;
+            for (int y = 0; y < 8; ++y) acc += __mul24(mv[y], T[wave][k][y * 8 + c]);   // |T| < 2^12
+            S[wave][k][zz] = quantise((acc + 8192) >> 14, k ? q1 : q0, k ? r1 : r0);    // zigzag order
+        }
+        wave_lds_fence();
+        for (int k = 0; k < 3; ++k) {
+            const int v = S[wave][k][lane];
+            coef[((size_t)mcu * 3 + k) * 64 + lane] = (int16_t)v;
+            const unsigned long long nz = __ballot(v != 0);
+            if (lane == 0) {
+                DC[1 + mcu - g0][k] = v;                   // its symbol below, from the difference
+            } else {
+                const LaneSym sy = lane_symbol(v, 0, nz, k != 0, lane);
+                if (sy.table >= 0) {
+                    atomicAdd(&H[sy.table * 256 + sy.sym], 1u);
+                    if (sy.zrl) atomicAdd(&H[sy.table * 256 + 0xF0], (unsigned)sy.zrl);
+                }
             }
-        __syncthreads();
-        if (live)
-            for (int k = 0; k < 3; ++k) {
-                int acc = 0;
-                for (int y = 0; y < 8; ++y) acc += __mul24(mv[y], T[wave][k][y * 8 + c]);   // |T| < 2^12
-                const int f = (acc + 8192) >> 14;
-                // |f| <= 1024 for 8-bit samples, so the dividend stays below 2^12 and the
-                // reciprocal product below 2^32 (24-bit operands)
-                const int q = k ? q1 : q0;
-                const unsigned a = (unsigned)((f < 0 ? -f : f) + (q >> 1));
-                const int mag = (int)(__umul24(a, k ? r1 : r0) >> 20);
-                coef[((size_t)mcu * 3 + k) * 64 + zz] = (int16_t)(f < 0 ? -mag : mag);
-            }
+        }
+        wave_lds_fence();                                  // S is read before the next MCU's samples
     }
-}
-
-// ---- 2. symbol counts ----
-
-__global__ __launch_bounds__(kThreads) void jpeg_hist_kernel(const int16_t* __restrict__ coef, int n_blocks,
-                                                             uint32_t* __restrict__ hist) {
-    __shared__ uint32_t H[kJpegTableCount * 256];
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
-    const int b0 = (blockIdx.x * kWaves + wave) * kBlocksPerWave;
-    const WaveBlocks wb = load_blocks(coef, b0, n_blocks, lane);
-    for (int i = threadIdx.x; i < kJpegTableCount * 256; i += kThreads) H[i] = 0;
     __syncthreads();
-    for (int i = 0; i < kBlocksPerWave; ++i) {
-        const int b = b0 + i;
-        const unsigned long long nz = __ballot(wb.v[i] != 0);
-        if (b >= n_blocks) break;
-        const LaneSym s = lane_symbol(wb.v[i], wb.prev[i], nz, (b % 3) != 0, lane);
-        if (s.table >= 0) {
-            atomicAdd(&H[s.table * 256 + s.sym], 1u);
-            if (s.zrl) atomicAdd(&H[s.table * 256 + 0xF0], (unsigned)s.zrl);
-        }
+    for (int i = threadIdx.x; i < kWaves * kMcuPerWave * 3; i += kThreads) {
+        const int m = i / 3, k = i - 3 * m;
+        if (g0 + m < n_mcu) atomicAdd(&H[(k ? 512 : 0) + category(DC[1 + m][k] - DC[m][k])], 1u);
     }
     __syncthreads();
     uint32_t* copy = hist + (blockIdx.x % kHistCopies) * (kJpegTableCount * 256);
@@ -731,8 +765,8 @@ int jpeg_encode(JpegWork* w, const uint8_t* rgba8, int width, int height, int qu
     const unsigned coef_groups = (unsigned)((n_mcu + kWaves * kMcuPerWave - 1) / (kWaves * kMcuPerWave));
     const bool same_a = w->a_rgba == rgba8 && w->a_width == width && w->a_height == height && w->a_gen == w->generation;
     JPEG_TRY(replay(w, &w->seg_a, same_a, s, [&](hipStream_t st) {
-        jpeg_coef_kernel<<<coef_groups, kThreads, 0, st>>>(rgba8, width, height, mcu_cols, n_mcu, w->tables, coef);
-        jpeg_hist_kernel<<<(unsigned)groups, kThreads, 0, st>>>(coef, n_blocks, w->hist);
+        jpeg_coef_kernel<<<coef_groups, kThreads, 0, st>>>(rgba8, width, height, mcu_cols, n_mcu, w->tables, coef,
+                                                           w->hist);
         jpeg_hist_reduce_kernel<<<kJpegTableCount * 256 / kThreads, kThreads, 0, st>>>(w->hist, w->host_hist);
         return hipGetLastError();
     }));
