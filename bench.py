@@ -15,7 +15,7 @@ memory before timing starts; `value` counts the scan points composited
 Also reported (not the headline): the same scene with FP16 and BF16 storage
 and in iso-surface mode, the RGBA8 frame encode, a field simulation on
 128^3 rendered in situ every step and every 10th step, the 64-sub-volume
-batch in one persistent hipGraph launch, and a short run of the
+batch in one hipGraph launch, and a short run of the
 continuous-batching server on a resident 512x512x256 volume.
 
 Prints one JSON line on stdout; progress goes to stderr.

@@ -244,8 +244,8 @@ isaac_status isaac_render(isaac_context* ctx, const isaac_render_desc* jobs, int
  *     whose volume covers up to 40 % of the screen).
  *   - No derived volume is built: a frozen volume's derived values are read
  *     (isaac_freeze_volume), other volumes are read in place, as with
- *     ISAAC_DIRECT.  Non-persistent sources are copied into the buffers
- *     isaac_set_sources allocated.
+ *     ISAAC_DIRECT.  Non-persistent sources are copied, where a call copies
+ *     them, into the buffers isaac_set_sources allocated.
  *   - Batches are launched directly (no hipGraph); no pooled schedule.
  *   - flags: ISAAC_ASYNC, ISAAC_NO_GRAPH, ISAAC_DIRECT; any other bit
  *     (ISAAC_TIMING, ISAAC_DERIVE) is ISAAC_ERR_INVALID_ARGUMENT.

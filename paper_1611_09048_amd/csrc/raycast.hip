@@ -1215,8 +1215,8 @@ __device__ __forceinline__ void march_dispatch(const DevJob& J, const float4* __
 // value between two consecutive scan points, placed by linear interpolation
 // between them; opaque, coloured by the source's table at the iso value and
 // lit by a headlight, 0.3 + 0.7 |cos| of the angle between the ray and the
-// central-difference gradient (half a voxel each side).  One lane per ray;
-// the source loop is uniform, so every source's buffer resource stays scalar.
+// central-difference gradient (half a voxel each side).  The source loop is
+// uniform, so every source's buffer resource stays scalar.
 // The crossing of source s between scan points k - 1 and k, at fraction f of
 // the step: opaque, the source's table colour at its iso value lit by a
 // headlight from the central-difference gradient (half a voxel each side).

@@ -8,7 +8,8 @@ step is short (Sec. 3.6, the Petri net of the render cycle).  Before each
 render the library calls every source's update() (Sec. 3.2), which here
 derives a secondary field into a scratch buffer; that source is declared
 non-persistent, so the library copies it before the next source's update
-could reuse the buffer.
+could reuse the buffer, or reads it in place where no update follows before
+the image is complete.
 
 `FieldSimulation` stands in for the host application (the paper couples the
 renderer to a particle-in-cell code, Sec. 4): an electric and a magnetic
@@ -146,7 +147,7 @@ class InSituRenderer:
         self.updates.append((src, int(enabled)))
         if src == 2 and enabled:
             # enqueued on torch's current stream, which the context shares (its default),
-            # so the library's copy of this source, next on that stream, reads the result
+            # so the library's reads of this source, next on that stream, see the result
             self.sim.derive_current()
 
     def render(self, desc: binding.RenderDesc) -> None:
