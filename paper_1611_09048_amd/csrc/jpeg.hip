@@ -384,11 +384,24 @@ __device__ inline unsigned long long block_sum_before(const unsigned long long* 
     return all;
 }
 
-// The frame's codes and code lengths from pinned host memory.
+// Where the coded bytes go: pinned host memory as far as it reaches, chunks that
+// would pass its end to device memory at the same positions.
+struct StuffOut {
+    uint8_t* host;
+    unsigned long long host_cap;
+    uint8_t* dev;
+    // pinned: coded bits, 0xFF bytes, and the position from which the bytes are in dev
+    unsigned long long* totals;
+};
+
+// The frame's codes and code lengths, and where its bytes go, from pinned host memory.
 __global__ __launch_bounds__(kThreads) void jpeg_tables_kernel(const uint32_t* __restrict__ host_codes,
                                                                const uint32_t* __restrict__ host_lens,
+                                                               const StuffOut* __restrict__ host_place,
                                                                uint32_t* __restrict__ codes,
-                                                               uint32_t* __restrict__ lens) {
+                                                               uint32_t* __restrict__ lens,
+                                                               StuffOut* __restrict__ place) {
+    if (threadIdx.x == 0) *place = *host_place;
     uint32_t c[kJpegTableCount];
     for (int k = 0; k < kJpegTableCount; ++k) c[k] = host_codes[k * kThreads + threadIdx.x];
     const uint32_t l = host_lens[threadIdx.x];
@@ -514,16 +527,6 @@ __global__ __launch_bounds__(kThreads) void stuff_count_kernel(const uint32_t* _
     }
 }
 
-// Where the coded bytes go: pinned host memory as far as it reaches, chunks that
-// would pass its end to device memory at the same positions.
-struct StuffOut {
-    uint8_t* host;
-    unsigned long long host_cap;
-    uint8_t* dev;
-    // pinned: coded bits, 0xFF bytes, and the position from which the bytes are in dev
-    unsigned long long* totals;
-};
-
 // Copies each chunk of stream with a 0x00 behind every 0xFF: the bytes are placed
 // in LDS first, then stored as aligned words (bytes at the ends).  A chunk's
 // position is its start plus the 0xFF bytes of the chunks before it.  The stream's
@@ -531,8 +534,9 @@ struct StuffOut {
 __global__ __launch_bounds__(kThreads) void stuff_write_kernel(uint32_t* __restrict__ words,
                                                                const unsigned long long* __restrict__ total_bits,
                                                                const unsigned long long* __restrict__ counts,
-                                                               int scanned, StuffOut out) {
+                                                               int scanned, const StuffOut* __restrict__ place) {
     __shared__ uint8_t L[2 * kStuffChunk];
+    const StuffOut out = *place;
     const unsigned long long bits = *total_bits, n_bytes = (bits + 7) / 8;
     for (unsigned long long chunk = blockIdx.x; chunk * kStuffChunk < n_bytes; chunk += gridDim.x) {
         const unsigned long long c0 = chunk * kStuffChunk;
@@ -579,6 +583,15 @@ __global__ __launch_bounds__(kThreads) void stuff_write_kernel(uint32_t* __restr
     }
 }
 
+// What passed the pinned buffer, into the larger one: n 16-byte words.  (The first
+// device-to-host copy of a process took 8 ms here.)
+__global__ __launch_bounds__(kThreads) void jpeg_rest_kernel(const uint4* __restrict__ dev, uint4* __restrict__ host,
+                                                             unsigned long long n) {
+    for (unsigned long long i = (unsigned long long)blockIdx.x * kThreads + threadIdx.x; i < n;
+         i += (unsigned long long)gridDim.x * kThreads)
+        host[i] = dev[i];
+}
+
 __global__ void fill_u32_kernel(uint32_t* __restrict__ p, long long n) {
     for (long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (long long)gridDim.x * blockDim.x)
         p[i] = 0u;
@@ -594,6 +607,8 @@ struct JpegWork {
     unsigned long long* total_bits = nullptr;   // device
     uint32_t* host_hist = nullptr;       // pinned [4][256]
     unsigned long long* host_totals = nullptr;  // pinned [3]: coded bits, 0xFF bytes, bytes in host_out
+    StuffOut* host_place = nullptr;      // pinned
+    StuffOut* place = nullptr;           // device
     uint32_t* host_codes = nullptr;      // pinned [4][256]
     uint8_t* host_lens = nullptr;        // pinned [4][256]
     uint8_t* host_out = nullptr;         // pinned: the coded bytes, written by the device
@@ -630,18 +645,18 @@ hipError_t grow(JpegWork* w, int i, size_t bytes) {
     return e;
 }
 
-// The pinned output buffer at `bytes` or more, keeping its first `keep` bytes.
-hipError_t grow_host(JpegWork* w, size_t bytes, size_t keep) {
-    if (bytes <= w->host_out_cap) return hipSuccess;
+// The pinned output buffer at `bytes` or more (its contents are lost); without the
+// memory it stays as it is, and what does not fit comes through device memory.
+void grow_host(JpegWork* w, size_t bytes) {
+    if (bytes <= w->host_out_cap) return;
     void* p = nullptr;
-    hipError_t e = hipHostMalloc(&p, bytes);
-    if (e != hipSuccess) return e;
-    if (keep) memcpy(p, w->host_out, keep);
-    if (w->host_out) e = hipHostFree(w->host_out);
+    if (hipHostMalloc(&p, bytes) != hipSuccess) {
+        (void)hipGetLastError();         // dealt with: not the next launch's error
+        return;
+    }
+    if (w->host_out) (void)hipHostFree(w->host_out);
     w->host_out = static_cast<uint8_t*>(p);
     w->host_out_cap = bytes;
-    ++w->generation;
-    return e;
 }
 
 // Replays *exec on stream s, first capturing `enqueue` into it on the work's
@@ -688,6 +703,8 @@ void jpeg_work_destroy(JpegWork* w) {
     if (w->total_bits) hipFree(w->total_bits);
     if (w->host_hist) hipHostFree(w->host_hist);
     if (w->host_totals) hipHostFree(w->host_totals);
+    if (w->host_place) hipHostFree(w->host_place);
+    if (w->place) hipFree(w->place);
     if (w->host_codes) hipHostFree(w->host_codes);
     if (w->host_out) hipHostFree(w->host_out);
     delete w;
@@ -727,6 +744,8 @@ int jpeg_encode(JpegWork* w, const uint8_t* rgba8, int width, int height, int qu
         JPEG_TRY(hipHostMalloc(reinterpret_cast<void**>(&w->host_hist), kJpegTableCount * 256 * sizeof(uint32_t)));
         JPEG_TRY(hipHostMalloc(reinterpret_cast<void**>(&w->host_codes), kJpegTableCount * 256 * sizeof(uint32_t)));
         JPEG_TRY(hipHostMalloc(reinterpret_cast<void**>(&w->host_totals), 3 * sizeof(unsigned long long)));
+        JPEG_TRY(hipHostMalloc(reinterpret_cast<void**>(&w->host_place), sizeof(StuffOut)));
+        JPEG_TRY(hipMalloc(&w->place, sizeof(StuffOut)));
         JPEG_TRY(hipStreamCreateWithFlags(&w->capture, hipStreamNonBlocking));
     }
     if (w->quality != quality) {
@@ -751,9 +770,14 @@ int jpeg_encode(JpegWork* w, const uint8_t* rgba8, int width, int height, int qu
     }
     JPEG_TRY(grow(w, B_STUFF, (size_t)stuff_groups * sizeof(unsigned long long)));
     JPEG_TRY(grow(w, B_OUT, (size_t)stuff_groups * kStuffChunk * 2));
-    // a byte per pixel holds the stream of all but noise; one that passes it comes
-    // through device memory, and the pinned buffer grows for the next
-    JPEG_TRY(grow_host(w, std::max<size_t>((size_t)width * height, 64 << 10), 0));
+    // A byte per pixel (a shaded body takes 0.02 to 0.1, a busy picture 0.3, noise 0.5 to
+    // 3), but at most 8 MiB, before any stream is known: unbounded, the largest frames held
+    // 1.4 GB that few streams use, and could not be encoded without it.  A stream that
+    // passes the pinned buffer comes through device memory, and the buffer grows to its
+    // size and a quarter for the next.  First calls of a context, 13.6 MB of noise at
+    // 3840 x 2160: 18.4 ms, then 1.05, with a byte per pixel and the rest by a copy; 6.5 ms,
+    // then 3.7 (the larger buffer is new), now; 0.98 from the third on either way.
+    grow_host(w, std::min<size_t>(std::max<size_t>((size_t)width * height, 64 << 10), 8 << 20));
     auto* coef = static_cast<int16_t*>(w->buf[B_COEF]);
     auto* bits = static_cast<uint32_t*>(w->buf[B_BITS]);
     auto* group = static_cast<unsigned long long*>(w->buf[B_GROUP]);
@@ -788,17 +812,17 @@ int jpeg_encode(JpegWork* w, const uint8_t* rgba8, int width, int height, int qu
     // offsets by summing what comes before, or scanned where that would be long
     const int scan_groups = groups > kMaxSummedGroups, scan_chunks = stuff_groups > kMaxSummedChunks;
     const unsigned stuff_grid = (unsigned)std::min<long long>(stuff_groups, kStuffGrid);
+    *w->host_place = StuffOut{w->host_out, w->host_out_cap, dst, w->host_totals};
     JPEG_TRY(replay(w, &w->seg_b, same_b, s, [&](hipStream_t st) {
         jpeg_tables_kernel<<<1, kThreads, 0, st>>>(w->host_codes, reinterpret_cast<const uint32_t*>(w->host_lens),
-                                                   w->codes, w->lens);
+                                                   w->host_place, w->codes, w->lens, w->place);
         jpeg_bits_kernel<<<(unsigned)groups, kThreads, 0, st>>>(coef, n_blocks, w->lens, bits, group);
         if (scan_groups) scan_top_kernel<<<1, kThreads, 0, st>>>(group, groups, nullptr);
         jpeg_pack_kernel<<<(unsigned)groups, kThreads, 0, st>>>(coef, n_blocks, w->codes, bits, group, scan_groups,
                                                                 words, w->total_bits);
         stuff_count_kernel<<<stuff_grid, kThreads, 0, st>>>(words, w->total_bits, ffcnt);
         if (scan_chunks) scan_top_kernel<<<1, kThreads, 0, st>>>(ffcnt, stuff_groups, w->total_bits);
-        stuff_write_kernel<<<stuff_grid, kThreads, 0, st>>>(
-            words, w->total_bits, ffcnt, scan_chunks, StuffOut{w->host_out, w->host_out_cap, dst, w->host_totals});
+        stuff_write_kernel<<<stuff_grid, kThreads, 0, st>>>(words, w->total_bits, ffcnt, scan_chunks, w->place);
         return hipGetLastError();
     }));
     w->b_blocks = n_blocks, w->b_gen = w->generation;
@@ -812,14 +836,23 @@ int jpeg_encode(JpegWork* w, const uint8_t* rgba8, int width, int height, int qu
     if (!out || capacity < need)
         return fail(ISAAC_ERR_INVALID_ARGUMENT, "output capacity below the stream size (written to out_size)",
                     hipSuccess);
-    const size_t in_host = (size_t)w->host_totals[2];
-    if (in_host < coded) {
-        JPEG_TRY(grow_host(w, coded, in_host));
-        JPEG_TRY(hipMemcpyAsync(w->host_out + in_host, dst + in_host, coded - in_host, hipMemcpyDeviceToHost, s));
-        JPEG_TRY(hipStreamSynchronize(s));
-    }
+    const size_t in_host = std::min((size_t)w->host_totals[2], coded), rest = coded - in_host;
     memcpy(out, hdr, hdr_len);
-    memcpy(out + hdr_len, w->host_out, coded);
+    if (in_host) memcpy(out + hdr_len, w->host_out, in_host);
+    if (rest) {
+        grow_host(w, (coded + coded / 4 + 15) & ~(size_t)15);
+        if (coded <= w->host_out_cap) {
+            const size_t from = in_host & ~(size_t)15, n = (coded - from + 15) / 16;    // both buffers go on to there
+            jpeg_rest_kernel<<<(unsigned)std::min<size_t>((n + kThreads - 1) / kThreads, 1024), kThreads, 0, s>>>(
+                reinterpret_cast<const uint4*>(dst + from), reinterpret_cast<uint4*>(w->host_out + from), n);
+            JPEG_TRY(hipGetLastError());
+            JPEG_TRY(hipStreamSynchronize(s));
+            memcpy(out + hdr_len + in_host, w->host_out + in_host, rest);
+        } else {
+            JPEG_TRY(hipMemcpyAsync(out + hdr_len + in_host, dst + in_host, rest, hipMemcpyDeviceToHost, s));
+            JPEG_TRY(hipStreamSynchronize(s));
+        }
+    }
     out[hdr_len + coded] = 0xFF;
     out[hdr_len + coded + 1] = 0xD9;                            // EOI
     return 0;

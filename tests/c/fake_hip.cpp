@@ -23,7 +23,7 @@ long long g_fail_host_from = -1;         // pinned allocations of at least this 
 long long g_fail_malloc_from = -1;       // device allocations of at least this many bytes fail
 std::string g_fail_call;                 // the next call of this name fails
 unsigned long long g_totals[3] = {0, 0, 0};
-hipError_t g_last = hipSuccess;
+hipError_t g_last = hipSuccess;          // as the runtime keeps it: a failed call's error, until it is asked for
 
 void note(const char* what, long long n = -1) {
     g_log += what;
@@ -86,7 +86,8 @@ hipError_t hipGetLastError() {
 
 hipError_t hipMalloc(void** p, size_t n) {
     note("malloc", (long long)n);
-    if (fails("hipMalloc") || (g_fail_malloc_from >= 0 && (long long)n >= g_fail_malloc_from)) return hipErrorOutOfMemory;
+    if (fails("hipMalloc") || (g_fail_malloc_from >= 0 && (long long)n >= g_fail_malloc_from))
+        return g_last = hipErrorOutOfMemory;
     *p = std::calloc(1, n);
     return *p ? hipSuccess : hipErrorOutOfMemory;
 }
@@ -98,7 +99,7 @@ hipError_t hipFree(void* p) {
 hipError_t hipHostMalloc(void** p, size_t n, unsigned) {
     note("hostmalloc", (long long)n);
     if (fails("hipHostMalloc") || (g_fail_host_from >= 0 && (long long)n >= g_fail_host_from))
-        return hipErrorOutOfMemory;
+        return g_last = hipErrorOutOfMemory;
     *p = std::calloc(1, n);
     g_host[*p] = n;
     return hipSuccess;
@@ -118,7 +119,7 @@ hipError_t hipMemcpyAsync(void* d, const void* s, size_t n, hipMemcpyKind, hipSt
 
 hipError_t hipStreamCreate(hipStream_t* s) { *s = handle<hipStream_t>(); return hipSuccess; }
 hipError_t hipStreamCreateWithFlags(hipStream_t* s, unsigned) {
-    if (fails("hipStreamCreateWithFlags")) return hipErrorOutOfMemory;
+    if (fails("hipStreamCreateWithFlags")) return g_last = hipErrorOutOfMemory;
     *s = handle<hipStream_t>();
     return hipSuccess;
 }
@@ -133,7 +134,7 @@ hipError_t hipGraphInstantiate(hipGraphExec_t* e, hipGraph_t, hipGraphNode_t*, c
 }
 hipError_t hipGraphLaunch(hipGraphExec_t, hipStream_t) {
     note("graph");
-    if (fails("hipGraphLaunch")) return hipErrorUnknown;
+    if (fails("hipGraphLaunch")) return g_last = hipErrorUnknown;
     for (auto& h : g_host)
         if (h.second == sizeof g_totals) std::memcpy(h.first, g_totals, sizeof g_totals);
     return hipSuccess;
@@ -141,7 +142,7 @@ hipError_t hipGraphLaunch(hipGraphExec_t, hipStream_t) {
 hipError_t hipGraphDestroy(hipGraph_t) { return hipSuccess; }
 hipError_t hipGraphExecDestroy(hipGraphExec_t) { return hipSuccess; }
 hipError_t hipEventCreate(hipEvent_t* e) {
-    if (fails("hipEventCreate")) return hipErrorOutOfMemory;
+    if (fails("hipEventCreate")) return g_last = hipErrorOutOfMemory;
     *e = handle<hipEvent_t>();
     return hipSuccess;
 }
