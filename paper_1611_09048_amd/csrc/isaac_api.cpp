@@ -123,6 +123,16 @@ struct Ticket {
     bool done = false;
 };
 
+// Device memory that the caller can do without or report the lack of.  The
+// runtime keeps a failed call's error until it is asked for: left there, the next
+// launch's check would find it and fail a call that has what it needs.
+bool try_malloc(void** p, size_t bytes) {
+    if (hipMalloc(p, bytes) == hipSuccess) return true;
+    (void)hipGetLastError();
+    *p = nullptr;
+    return false;
+}
+
 // Serving images: one device allocation of the memory budget, made at the
 // first submission and carved into images first fit (256-byte granules, free
 // neighbours merged on release), so no request allocates or frees device
@@ -133,7 +143,7 @@ public:
     bool ready() const { return base_ != nullptr; }
     bool init(size_t bytes) {
         bytes = bytes / kGranule * kGranule;
-        if (bytes == 0 || hipMalloc((void**)&base_, bytes) != hipSuccess) {
+        if (bytes == 0 || !try_malloc((void**)&base_, bytes)) {
             base_ = nullptr;
             return false;
         }
@@ -661,7 +671,7 @@ isaac_status acquire_slot(isaac_context* ctx, RingSlot** out) {
 
 // Ray buffer and counters of the pooled schedule, grown to `bytes`.
 bool ensure_pool(isaac_context* ctx, size_t bytes, hipStream_t stream) {
-    if (!ctx->pool_counters && hipMalloc(&ctx->pool_counters, 2 * sizeof(int)) != hipSuccess) {
+    if (!ctx->pool_counters && !try_malloc((void**)&ctx->pool_counters, 2 * sizeof(int))) {
         ctx->pool_counters = nullptr;
         return false;
     }
@@ -672,7 +682,7 @@ bool ensure_pool(isaac_context* ctx, size_t bytes, hipStream_t stream) {
     }
     ctx->pool_rays = nullptr;
     ctx->pool_bytes = 0;
-    if (hipMalloc(&ctx->pool_rays, bytes) != hipSuccess) {
+    if (!try_malloc(&ctx->pool_rays, bytes)) {
         ctx->pool_rays = nullptr;
         return false;
     }
@@ -1002,7 +1012,7 @@ isaac_status derive_volumes(isaac_context* ctx, const isaac_render_desc* jobs, s
             }
             v.derived = nullptr;
             v.derived_bytes = 0;
-            if (hipMalloc(&v.derived, bytes) != hipSuccess) {
+            if (!try_malloc(&v.derived, bytes)) {
                 v.derived = nullptr;
                 continue;             // no memory: read the sources directly
             }
@@ -1387,7 +1397,7 @@ isaac_status isaac_set_sources(isaac_context* ctx, int volume_id, const int32_t 
             return set_err(ctx, ISAAC_ERR_INVALID_ARGUMENT, "non-persistent source '%s' larger than 2 GiB",
                            h.name.c_str());
         }
-        if (hipMalloc(&h.shadow, h.shadow_bytes) != hipSuccess) {
+        if (!try_malloc(&h.shadow, h.shadow_bytes)) {
             for (auto& x : hs)
                 if (x.shadow) hipFree(x.shadow);
             return set_err(ctx, ISAAC_ERR_OUT_OF_MEMORY, "no memory for the copy of source '%s'", h.name.c_str());
