@@ -352,9 +352,10 @@ isaac_status isaac_timing(isaac_context* ctx, double* total_ms, int* count);
  * A batch runs one launch per distinct schedule, so each job is rendered as
  * it would be alone.
  * Defaults: (8, 2, 1, 1, 0, 0).  One lane per ray fixes the arithmetic, a ray's
- * points composited one after another; the points are evaluated by groups of 4
- * or 16 lanes, whichever suits the number of rays (a wave then holds 16 or 4 of
- * them).  Settings with one lane per ray give the same image bit for bit; more
+ * points composited one after another; the points are evaluated by one lane or by
+ * groups of 4 or 16, whichever suits the number of rays and how many points they
+ * are expected to take (a wave then holds 64, 16 or 4 rays).
+ * Settings with one lane per ray give the same image bit for bit; more
  * lanes composite each row of scan points by a scan, which changes only FP32
  * rounding; a given setting always reproduces its image bit for bit. */
 isaac_status isaac_set_tile_shape(isaac_context* ctx, int size_class, int wave_w, int waves_x, int unroll,

@@ -233,5 +233,22 @@ void set_cull_rect(DevJob& dj) {
     dj.cull[3] = (int)clampd(std::ceil(ymax) + 1.0, -1.0, (double)dj.height - 1);
 }
 
+// A group gains where a lane alone would wait on many gathers one after another, and
+// loses where most of a row lies past the ray's end or its termination and the rays
+// fill the chip without it.  The lines lie where the times cross on 400 single calls
+// (256 x 256 to 3840 x 2160, volumes of 16^3 to 160^3, one to four sources, opacities of
+// 0.015 to 1) and 100 batches, on the side of the groups, whose gain is the larger.  us a
+// call with 1, 4 and 16 lanes, by rays and points: 6.7 K rays, 77 points 98, 41, 25; 27 K,
+// 1 point (in place) 22.5, 24.6, 33.9, 77 points 88, 43, 32; 61 K, 1 point 21.2, 22.4,
+// 30.8, 77 points (three sources) 140, 71, 67; 120 K, 1 point 25, 28, 44, 3 points 33,
+// 36, 55, 20 points 40, 34, 49, 177 points 303, 183, 180; 480 K, 1 point 46, 57, 115, 10
+// points 57, 69, 129, 39 points (three sources) 176, 148, 198, 191 points 662, 429, 475; a
+// batch of 135 K rays in place, 83 points 2250, 853, 601; one of 670 K, 58 points 371,
+// 218, 321.
+int lanes_in_order(double rays, double points) {
+    if (rays > 27000.0 * points) return 1;
+    return rays < 190000.0 && rays <= 2600.0 * points ? 16 : 4;
+}
+
 }  // namespace host
 }  // namespace isaac

@@ -41,5 +41,10 @@ bool camera_basis(const isaac_render_desc& j, CameraBasis& cb, std::string& err)
 // the eye plane.
 void set_cull_rect(DevJob& dj);
 
+// Lanes that evaluate a ray of the one-lane schedule in a launch of `rays` rays that
+// take `points` scan points each, about: 1, or a group of 4 or 16 whose points are
+// composited in order.  Every choice gives the same image.
+int lanes_in_order(double rays, double points);
+
 }  // namespace host
 }  // namespace isaac

@@ -33,18 +33,12 @@ using isaac::host::camera_basis;
 using isaac::host::CameraBasis;
 using isaac::host::compile_chain;
 using isaac::host::CompiledChain;
+using isaac::host::lanes_in_order;
 using isaac::host::set_cull_rect;
 
 namespace {
 
 constexpr int kRingSlots = 16;
-// Jobs of one lane per ray: the rays of a launch from which groups of 4 lanes
-// evaluate them instead of 16.  Few rays need 16 to fill the chip; many are as fast
-// or faster with 4, whose in-order compositing takes a quarter of the instructions
-// per point.  Measured, us a call for 4 and 16 lanes: 36 K rays (512^2, one scalar) 47
-// and 38; 92 K (720p, three derived sources) 74 and 77, (four) 139 and 129; 217 K
-// (1080p, three) 236 and 234; 867 K (4K, three) 405 and 466.
-constexpr size_t kOrderedWideRays = 1 << 18;
 constexpr int kTfSlots = 4096;      // transfer tables resident at once (16 MiB)
 
 struct Status {
@@ -90,6 +84,7 @@ struct Volume {
 };
 
 struct TfSlot {
+    float opacity = 0.f;            // mean over the table
     bool live = false;              // allocated (referenced by a handle)
     bool released = false;
     uint64_t last_use = 0;          // render sequence number that last read it
@@ -333,6 +328,9 @@ isaac_status new_tf_slot(isaac_context* ctx, const float* table, int32_t* handle
                            hipMemcpyHostToDevice));
     ctx->tf_slots[slot] = TfSlot();
     ctx->tf_slots[slot].live = true;
+    double opacity = 0.0;
+    for (int j = 0; j < kTfEntries; ++j) opacity += table[4 * j + 3];
+    ctx->tf_slots[slot].opacity = (float)(opacity / kTfEntries);
     *handle = slot;
     return ISAAC_OK;
 }
@@ -690,6 +688,51 @@ bool ensure_pool(isaac_context* ctx, size_t bytes, hipStream_t stream) {
     return true;
 }
 
+// Scan points a job is expected to take before clipping and termination:
+// the volume's cells over the step, times the rays per cell cross-section at
+// the volume's centre.
+double estimate_samples(const DevJob& dj) {
+    const double cells = (double)dj.dims[0] * dj.dims[1] * dj.dims[2];
+    double px;   // pixels per voxel across the view at the volume centre
+    if (dj.ortho) {
+        px = dj.height / (2.0 * dj.h);
+    } else {
+        double r2 = 0.0;
+        for (int a = 0; a < 3; ++a) {
+            const double c = dj.org[a] + 0.5 * dj.dims[a] - dj.eye[a];
+            r2 += c * c;
+        }
+        px = dj.height / (2.0 * std::sqrt(std::max(r2, 1.0)) * dj.h);
+    }
+    return cells / dj.step * std::min(px * px, 1.0e6);
+}
+
+size_t rect_pixels(const DevJob& dj) {
+    return (size_t)std::max(0, dj.cull[2] - dj.cull[0] + 1) * std::max(0, dj.cull[3] - dj.cull[1] + 1);
+}
+
+// Rays of the job expected to meet its box (the box's shadow along the line of sight to
+// its centre, at most the screen rectangle), and the scan points such a ray is expected
+// to take, to the box's end or to its termination as if the sources' values were spread
+// evenly over their tables.
+void expected_rays(const isaac_context* ctx, const DevJob& dj, double& rays, double& points) {
+    double d[3], r = 0.0, diag = 0.0, shadow = 0.0, opacity = 0.0;
+    for (int a = 0; a < 3; ++a) {
+        d[a] = dj.ortho ? dj.fwd[a] : dj.org[a] + 0.5 * dj.dims[a] - dj.eye[a];
+        r += d[a] * d[a];
+        diag += (double)dj.dims[a] * dj.dims[a];
+    }
+    const double cells = (double)dj.dims[0] * dj.dims[1] * dj.dims[2], samples = estimate_samples(dj);
+    for (int a = 0; a < 3; ++a) shadow += std::abs(d[a]) / std::sqrt(std::max(r, 1e-12)) * cells / dj.dims[a];
+    // (samples / cells * step: pixels per cell cross-section)
+    rays = std::min((double)rect_pixels(dj), shadow * (samples / cells * dj.step));
+    points = rays > 0.0 ? std::min(samples / rays, std::sqrt(diag) / dj.step) : 0.0;
+    for (int s = 0; s < dj.n_src; ++s) opacity += dj.src[s].weight * ctx->tf_slots[dj.src[s].tf_slot].opacity;
+    if (dj.ert > 1.f || opacity <= 0.0) return;
+    const double left = std::max(1.0 - dj.ert, 1e-7);      // transparency at which the ray ends
+    points = std::min(points, std::max(1.0, std::log(left) / std::log(1.0 - std::min(opacity, 0.999))));
+}
+
 // noalloc: the call may not allocate: the set-up pass writes its ray records
 // into the context device's static scratch (the caller checked they fit), no
 // pooled schedule, no hipGraph, and the staging ring's event marks completion.
@@ -703,10 +746,14 @@ isaac_status enqueue_jobs(isaac_context* ctx, const isaac_render_desc* jobs, con
     int lanes = djs[0].lanes, hint = djs[0].waves_hint;
     const bool ordered = lanes == 1;
     if (ordered) {
-        size_t rays = 0;
-        for (const DevJob& dj : djs)
-            rays += (size_t)std::max(0, dj.cull[2] - dj.cull[0] + 1) * std::max(0, dj.cull[3] - dj.cull[1] + 1);
-        lanes = rays < kOrderedWideRays ? 16 : 4;
+        double rays = 0.0, points = 0.0;
+        for (const DevJob& dj : djs) {
+            double n, p;
+            expected_rays(ctx, dj, n, p);
+            rays += n;
+            points += n * p;
+        }
+        lanes = lanes_in_order(rays, rays > 0.0 ? points / rays : 0.0);
     }
     int tiles = 0;
     for (int i = 0; i < n; ++i) {
@@ -869,25 +916,6 @@ isaac_status enqueue_jobs(isaac_context* ctx, const isaac_render_desc* jobs, con
     HIP_TRY(ctx, hipEventRecord(pe, stream));
     ctx->pending.push_back({seq, pe});
     return ISAAC_OK;
-}
-
-// Scan points a job is expected to take before clipping and termination:
-// the volume's cells over the step, times the rays per cell cross-section at
-// the volume's centre.
-double estimate_samples(const DevJob& dj) {
-    const double cells = (double)dj.dims[0] * dj.dims[1] * dj.dims[2];
-    double px;   // pixels per voxel across the view at the volume centre
-    if (dj.ortho) {
-        px = dj.height / (2.0 * dj.h);
-    } else {
-        double r2 = 0.0;
-        for (int a = 0; a < 3; ++a) {
-            const double c = dj.org[a] + 0.5 * dj.dims[a] - dj.eye[a];
-            r2 += c * c;
-        }
-        px = dj.height / (2.0 * std::sqrt(std::max(r2, 1.0)) * dj.h);
-    }
-    return cells / dj.step * std::min(px * px, 1.0e6);
 }
 
 // Replace the sources of the call's jobs by derived volumes where that saves

@@ -941,6 +941,31 @@ __device__ __forceinline__ void over_in_order(const float (&E)[3], float S, floa
 }
 #undef ISAAC_OVER
 
+// One lane per ray: its scan points one after another, front to back, to the first
+// whose opacity reaches ert.  For launches of many rays that end after a few points:
+// a row of points evaluated together (below) is mostly wasted on those, and the
+// groups' waves are so many that starting them is the time (an opaque scalar at 1920 x
+// 1080: 25 us a call against 44 with 16 lanes, 29 with 4; at 4K 46 against 58 with 4).
+template <int INTERP, int SIG, bool PS>
+__device__ __forceinline__ void march_one(const DevJob& J, const float4* __restrict__ s_tf, const RaySetup& R,
+                                          float4& out, int& count) {
+    float C0 = 0.f, C1 = 0.f, C2 = 0.f, A = 0.f;
+    int n = 0;
+    for (int k = R.kb; k < R.ke; ++k) {
+        float E[3], S;
+        point<INTERP, SIG, PS>(J, s_tf, R, k, E, S);
+        const float T = 1.f - A;
+        C0 = fmaf(E[0], T, C0);
+        C1 = fmaf(E[1], T, C1);
+        C2 = fmaf(E[2], T, C2);
+        A = fmaf(S, T, A);
+        ++n;
+        if (A >= J.ert) break;
+    }
+    out = make_float4(C0, C1, C2, A);
+    count = n;
+}
+
 // One lane per ray as far as the image goes: the scan points of a ray are
 // composited one after another, front to back, with early termination at the
 // first whose opacity reaches ert.  They are evaluated by a group of G lanes, a
@@ -1187,7 +1212,8 @@ __device__ __forceinline__ void march_lanes(const DevJob& J, const float4* __res
 template <int INTERP, bool ORD, int G, int SIG, bool PS>
 __device__ __forceinline__ void march_sig(const DevJob& J, const float4* __restrict__ s_tf, const RaySetup& R,
                                           int lane, float4& out, int& count) {
-    if constexpr (ORD) march_ordered<INTERP, G, SIG, PS>(J, s_tf, R, lane, out, count);
+    if constexpr (ORD && G == 1) march_one<INTERP, SIG, PS>(J, s_tf, R, out, count);
+    else if constexpr (ORD) march_ordered<INTERP, G, SIG, PS>(J, s_tf, R, lane, out, count);
     else if constexpr (Il<SIG>::n > 0 && !PS) march_lanes_il<INTERP, G, SIG>(J, s_tf, R, lane, out, count);
     else march_lanes<INTERP, G, SIG, PS>(J, s_tf, R, lane, out, count);
 }
@@ -2040,13 +2066,16 @@ using KernelFn = void (*)(const DevJob*, const float4*, int, int);
 template <int SIGK>
 constexpr int kHintW = Il<SIGK>::n >= 3 || SIGK == SIG_GENERIC ? 4 : 0;
 
-// ordered: the image of one lane per ray, by groups of 4 or 16 lanes
+// ordered: the image of one lane per ray, by one lane or groups of 4 or 16
 template <int SIGK>
 KernelFn pick_specialized(int ordered, int lanes, int hint) {
     constexpr int H = kHintW<SIGK>;
     // the general loop would spill under a bound of 4 waves with the composited row beside it
     constexpr int O = SIGK == SIG_GENERIC ? 0 : H;
-    if (ordered) return lanes == 4 ? raycast_kernel<true, 4, O, SIGK> : raycast_kernel<true, 16, O, SIGK>;
+    if (ordered)
+        return lanes == 1   ? raycast_kernel<true, 1, O, SIGK>
+               : lanes == 4 ? raycast_kernel<true, 4, O, SIGK>
+                            : raycast_kernel<true, 16, O, SIGK>;
     switch (lanes) {
     case 64: return raycast_kernel<false, 64, 0, SIGK>;
     case 32: return raycast_kernel<false, 32, 0, SIGK>;
@@ -2077,7 +2106,10 @@ KernelFn pick_kernel(int mode, int sig, int ordered, int lanes, int hint) {
         break;
     }
     // mixed signatures: the dispatching kernels (one lane-count each)
-    if (ordered) return lanes == 4 ? raycast_kernel<true, 4, 0, -1> : raycast_kernel<true, 16, 0, -1>;
+    if (ordered)
+        return lanes == 1   ? raycast_kernel<true, 1, 0, -1>
+               : lanes == 4 ? raycast_kernel<true, 4, 0, -1>
+                            : raycast_kernel<true, 16, 0, -1>;
     switch (lanes) {
     case 64: return raycast_kernel<false, 64, 0, -1>;
     case 32: return raycast_kernel<false, 32, 0, -1>;
