@@ -250,5 +250,13 @@ int lanes_in_order(double rays, double points) {
     return rays < 190000.0 && rays <= 2600.0 * points ? 16 : 4;
 }
 
+// Eight lanes find a crossing in an eighth of the dependent steps, and evaluate up to 7
+// points beyond it: many rays of few points fill the chip without them.  us a call
+// with 1 and 8 lanes, surfaces in the middle of the volume and none at all: 120 K rays,
+// 19 points 71, 57 and 96, 76; 480 K rays, 19 points 109, 142 and 154, 199, 39 points
+// 100, 145 and 295, 336, 77 points 117, 148 and 772, 631, 191 points 163, 179 and 2642,
+// 1717.
+int lanes_iso(double rays, double points) { return rays >= 283000.0 && points < 100.0 ? 1 : 8; }
+
 }  // namespace host
 }  // namespace isaac

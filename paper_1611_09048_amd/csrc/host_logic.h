@@ -46,5 +46,9 @@ void set_cull_rect(DevJob& dj);
 // composited in order.  Every choice gives the same image.
 int lanes_in_order(double rays, double points);
 
+// Lanes per ray of iso-surface jobs whose schedule does not ask for 8 or more: 1 or 8,
+// for the same image.
+int lanes_iso(double rays, double points);
+
 }  // namespace host
 }  // namespace isaac

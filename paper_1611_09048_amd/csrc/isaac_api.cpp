@@ -34,6 +34,7 @@ using isaac::host::CameraBasis;
 using isaac::host::compile_chain;
 using isaac::host::CompiledChain;
 using isaac::host::lanes_in_order;
+using isaac::host::lanes_iso;
 using isaac::host::set_cull_rect;
 
 namespace {
@@ -587,12 +588,12 @@ isaac_status build_job(isaac_context* ctx, const isaac_render_desc& j, bool need
     dj.mode = j.mode;
     dj.sig = signature_of(dj);
     if (dj.mode == ISAAC_ISO) {
-        // iso jobs run their own kernel with the runtime source loop, 8 lanes per
-        // ray (the image is that of one lane, bit for bit)
+        // iso jobs run their own kernel with the runtime source loop: 8 lanes per ray,
+        // or 1 where that is the faster (the image is that of one lane, bit for bit)
         dj.sig = SIG_GENERIC;
         dj.waves_hint = 0;
         dj.pool = 0;
-        set_tiles(dj, 8);
+        set_tiles(dj, ts.lanes >= 8 ? 8 : 1);
     }
     *n_active_out = n_act;
     return ISAAC_OK;
@@ -728,7 +729,7 @@ void expected_rays(const isaac_context* ctx, const DevJob& dj, double& rays, dou
     rays = std::min((double)rect_pixels(dj), shadow * (samples / cells * dj.step));
     points = rays > 0.0 ? std::min(samples / rays, std::sqrt(diag) / dj.step) : 0.0;
     for (int s = 0; s < dj.n_src; ++s) opacity += dj.src[s].weight * ctx->tf_slots[dj.src[s].tf_slot].opacity;
-    if (dj.ert > 1.f || opacity <= 0.0) return;
+    if (dj.mode == ISAAC_ISO || dj.ert > 1.f || opacity <= 0.0) return;
     const double left = std::max(1.0 - dj.ert, 1e-7);      // transparency at which the ray ends
     points = std::min(points, std::max(1.0, std::log(left) / std::log(1.0 - std::min(opacity, 0.999))));
 }
@@ -744,8 +745,8 @@ isaac_status enqueue_jobs(isaac_context* ctx, const isaac_render_desc* jobs, con
     if (st) return st;
     // one kernel variant per launch (the caller groups jobs by schedule)
     int lanes = djs[0].lanes, hint = djs[0].waves_hint;
-    const bool ordered = lanes == 1;
-    if (ordered) {
+    const bool ordered = lanes == 1 && djs[0].mode != ISAAC_ISO;
+    if (lanes == 1) {
         double rays = 0.0, points = 0.0;
         for (const DevJob& dj : djs) {
             double n, p;
@@ -753,7 +754,8 @@ isaac_status enqueue_jobs(isaac_context* ctx, const isaac_render_desc* jobs, con
             rays += n;
             points += n * p;
         }
-        lanes = lanes_in_order(rays, rays > 0.0 ? points / rays : 0.0);
+        points = rays > 0.0 ? points / rays : 0.0;
+        lanes = ordered ? lanes_in_order(rays, points) : lanes_iso(rays, points);
     }
     int tiles = 0;
     for (int i = 0; i < n; ++i) {

@@ -1281,8 +1281,9 @@ __device__ __forceinline__ float4 iso_shade(const DevJob& J, const float4* __res
 // before), so every lane tests its own pair of consecutive points at once and
 // the ray's crossing is the first lane (then the first source in index order)
 // that sees one: the point, source and fraction the one-lane loop finds, with
-// the same arithmetic, in a fraction of its dependent steps.  The crossing's
-// lane shades, and passes colour and count to the group's first lane.
+// the same arithmetic, in a fraction of its dependent steps (G = 1 is that loop,
+// for launches of many short rays).  The crossing's lane shades, and passes colour
+// and count to the group's first lane.
 template <int INTERP, int G, bool PLAIN>
 __device__ __forceinline__ void march_iso_lanes(const DevJob& J, const float4* __restrict__ s_tf,
                                                 const RaySetup& R, int lane, float4& out, int& count) {
@@ -1301,13 +1302,16 @@ __device__ __forceinline__ void march_iso_lanes(const DevJob& J, const float4* _
         for (int s = 0; s < J.n_src; ++s) {
             const DevSource& S = J.src[s];
             const float x = sample_any<INTERP, PLAIN>(S, dims, p);
-            float prev = __shfl(x, base + ((g + G - 1) & (G - 1)), 64);
-            if (g == 0) prev = carry[s];
+            float prev = carry[s];
+            if constexpr (G > 1) {
+                const float below = __shfl(x, base + ((g + G - 1) & (G - 1)), 64);
+                if (g > 0) prev = below;
+            }
             if (my_s < 0 && valid && k > R.kb && ((prev >= S.iso) != (x >= S.iso))) {
                 my_s = s;
                 my_f = (S.iso - prev) / (x - prev);
             }
-            carry[s] = __shfl(x, base + G - 1, 64);
+            carry[s] = G > 1 ? __shfl(x, base + G - 1, 64) : x;
         }
         const unsigned long long bits = (__builtin_amdgcn_ballot_w64(my_s >= 0) >> base) & kGroupMask;
         if (bits) {
@@ -2089,7 +2093,10 @@ KernelFn pick_specialized(int ordered, int lanes, int hint) {
 KernelFn pick_kernel(int mode, int sig, int ordered, int lanes, int hint) {
     // iso-surface jobs: sig -3 when every source is plain (packed FP32 scalars without
     // functors, guard layers), else the run-time source handling
-    if (mode == 1) return sig == -3 ? raycast_kernel<false, 8, 0, -3> : raycast_kernel<false, 8, 0, -2>;
+    if (mode == 1) {
+        if (lanes == 1) return sig == -3 ? raycast_kernel<false, 1, 0, -3> : raycast_kernel<false, 1, 0, -2>;
+        return sig == -3 ? raycast_kernel<false, 8, 0, -3> : raycast_kernel<false, 8, 0, -2>;
+    }
     switch (sig) {
     case SIG_F32x1: return pick_specialized<SIG_F32x1>(ordered, lanes, hint);
     case SIG_PIC3_F32: return pick_specialized<SIG_PIC3_F32>(ordered, lanes, hint);

@@ -63,3 +63,30 @@ def test_opaque_view_agrees_with_the_oracle(content, size):
     with Context(device=0) as ctx:
         img, cnt = device.render_scene(ctx, sc)
     compare(img.reshape(-1, 4), cnt.reshape(-1), oracle.render(sc, threads=8), label=f"opaque {content} {size}")
+
+
+@pytest.mark.parametrize("interpolation", [0, 1])
+@pytest.mark.parametrize("kind", ["f32", "f16", "scalar"])
+def test_iso_by_one_and_eight_lanes_agree(kind, interpolation):
+    """Alone (8 lanes) and beside a large view (1 lane)."""
+    from paper_1611_09048_amd import Context, device
+    sc = configs.plain_scalar(n=20) if kind == "scalar" else configs.pic3(n=20, dtype=kind, n_clip=1)
+    iso = [0.3] if kind == "scalar" else [1.0, 0.2, 0.15]
+    sc = sc.with_(width=200, height=160, interpolation=interpolation, mode="iso",
+                  camera=configs.orbit_camera(sc.dims, (0.5, -0.7, 0.4), 0.75),
+                  sources=[dataclasses.replace(s, iso=v) for s, v in zip(sc.sources, iso)])
+    large = sc.with_(width=1200, height=1200)
+    with Context(device=0) as ctx:
+        keep = device.upload_volume(ctx, sc, 0)
+        got = []
+        for beside in (False, True):
+            img, cnt = device.new_image(sc), device.new_counts(sc)
+            jobs = [device.render_job(sc, 0, img, cnt)]
+            if beside:
+                side = device.new_image(large)
+                jobs.append(device.render_job(large, 0, side))
+            ctx.render(jobs)
+            got.append((img.cpu().numpy(), cnt.cpu().numpy()))
+        del keep
+    assert (got[0][0][..., 3] > 0).mean() > 0.1
+    assert np.array_equal(got[1][0], got[0][0]) and np.array_equal(got[1][1], got[0][1])

@@ -59,3 +59,18 @@ def test_a_batch_is_one_launch_and_an_empty_rectangle_counts_nothing(cpu):
     assert lanes(log) == [1]
     ctx.render([view(0, 64, 512, 512), view(1, 160, 512, 512)])
     assert lanes(log) == [16]
+
+
+@pytest.mark.parametrize("n,w,h,shape,want", [
+    (64, 256, 256, 1, 8), (16, 1920, 1080, 1, 8), (16, 3840, 2160, 1, 1), (32, 3840, 2160, 4, 1),
+    (160, 3840, 2160, 1, 8), (16, 3840, 2160, 16, 8)])
+def test_lanes_of_iso_jobs(cpu, n, w, h, shape, want):
+    from paper_1611_09048_amd import binding
+    ctx, log = cpu
+    for cls in range(16):
+        ctx.set_tile_shape(cls, 64 // shape if shape > 8 else 8, 1, 1, shape)
+    volume(ctx, 0, n, OPAQUE)
+    log()
+    ctx.render([view(0, n, w, h, mode=binding.ISO, iso_values=[0.5])])
+    got = [int(m.group(1)) for m in [re.search(r"raycast_kernelILb0ELi(\d+)ELi0ELin[23]E", line) for line in log()] if m]
+    assert got == [want]
