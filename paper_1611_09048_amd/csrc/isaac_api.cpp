@@ -1334,11 +1334,9 @@ void isaac_destroy(isaac_context* ctx) {
             if (s.shadow) hipFree(s.shadow);
         if (v.derived) hipFree(v.derived);
     }
-    for (auto& kv : ctx->tickets) {
-        if (kv.second.out) hipFree(kv.second.out);
+    for (auto& kv : ctx->tickets)
         if (kv.second.ev) hipEventDestroy(kv.second.ev);
-    }
-    ctx->images.destroy();
+    ctx->images.destroy();                // the tickets' images lie in it
     for (auto& r : ctx->ring) {
         if (r.exec) hipGraphExecDestroy(r.exec);
         if (r.graph) hipGraphDestroy(r.graph);

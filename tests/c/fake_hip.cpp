@@ -3,12 +3,14 @@
 // into a host-only build of the library, it shows which calls allocate, wait and
 // launch what, and lets a call fail, with no GPU.  Every call appends a line to a log:
 //   malloc BYTES | free | hostmalloc BYTES | hostfree | sync | launch KERNEL GX GY GZ
+//   bad CALL (a pointer or event that is not, or no longer, the library's)
 #include <hip/hip_runtime.h>
 
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
 #include <map>
+#include <set>
 #include <string>
 
 namespace {
@@ -19,9 +21,11 @@ std::map<const void*, std::string>& kernels() {     // filled while the library 
     return m;
 }
 std::map<void*, size_t> g_host;          // live pinned allocations
+std::set<void*> g_device, g_events;      // live device allocations and events
 long long g_fail_host_from = -1;         // pinned allocations of at least this many bytes fail
 long long g_fail_malloc_from = -1;       // device allocations of at least this many bytes fail
 std::string g_fail_call;                 // the next call of this name fails
+bool g_pending = false;                  // events are not complete when asked
 unsigned long long g_totals[3] = {0, 0, 0};
 hipError_t g_last = hipSuccess;          // as the runtime keeps it: a failed call's error, until it is asked for
 
@@ -56,6 +60,7 @@ void fake_clear() { g_log.clear(); }
 void fake_fail_host_from(long long bytes) { g_fail_host_from = bytes; }
 void fake_fail_malloc_from(long long bytes) { g_fail_malloc_from = bytes; }
 void fake_fail_call(const char* name) { g_fail_call = name; }
+void fake_pending(int on) { g_pending = on != 0; }
 unsigned long long fake_host_bytes() {
     unsigned long long n = 0;
     for (const auto& h : g_host) n += h.second;
@@ -89,10 +94,17 @@ hipError_t hipMalloc(void** p, size_t n) {
     if (fails("hipMalloc") || (g_fail_malloc_from >= 0 && (long long)n >= g_fail_malloc_from))
         return g_last = hipErrorOutOfMemory;
     *p = std::calloc(1, n);
-    return *p ? hipSuccess : hipErrorOutOfMemory;
+    if (!*p) return g_last = hipErrorOutOfMemory;
+    g_device.insert(*p);
+    return hipSuccess;
 }
 hipError_t hipFree(void* p) {
-    if (p) note("free");
+    if (!p) return hipSuccess;
+    note("free");
+    if (!g_device.erase(p)) {
+        note("bad hipFree");
+        return g_last = hipErrorInvalidValue;
+    }
     std::free(p);
     return hipSuccess;
 }
@@ -143,13 +155,24 @@ hipError_t hipGraphDestroy(hipGraph_t) { return hipSuccess; }
 hipError_t hipGraphExecDestroy(hipGraphExec_t) { return hipSuccess; }
 hipError_t hipEventCreate(hipEvent_t* e) {
     if (fails("hipEventCreate")) return g_last = hipErrorOutOfMemory;
-    *e = handle<hipEvent_t>();
+    *e = reinterpret_cast<hipEvent_t>(std::malloc(1));
+    g_events.insert(*e);
     return hipSuccess;
 }
 hipError_t hipEventCreateWithFlags(hipEvent_t* e, unsigned) { return hipEventCreate(e); }
-hipError_t hipEventDestroy(hipEvent_t) { return hipSuccess; }
-hipError_t hipEventQuery(hipEvent_t) { return hipSuccess; }
-hipError_t hipEventRecord(hipEvent_t, hipStream_t) { return hipSuccess; }
+hipError_t hipEventDestroy(hipEvent_t e) {
+    if (!g_events.erase(e)) {
+        note("bad hipEventDestroy");
+        return g_last = hipErrorInvalidHandle;
+    }
+    std::free(e);
+    return hipSuccess;
+}
+hipError_t hipEventQuery(hipEvent_t) { return g_pending ? hipErrorNotReady : hipSuccess; }
+hipError_t hipEventRecord(hipEvent_t e, hipStream_t) {
+    if (!g_events.count(e)) note("bad hipEventRecord");
+    return hipSuccess;
+}
 hipError_t hipEventSynchronize(hipEvent_t) { return hipSuccess; }
 hipError_t hipEventElapsedTime(float* ms, hipEvent_t, hipEvent_t) { *ms = 1.f; return hipSuccess; }
 hipError_t hipGetSymbolAddress(void** p, const void*) {

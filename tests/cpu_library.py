@@ -56,4 +56,7 @@ def cpu(cpu_lib, monkeypatch):
     cpu_lib.fake_fail_malloc_from(-1)
     cpu_lib.fake_fail_call(b"")
     cpu_lib.fake_graph_totals(0, 0, 0)
+    cpu_lib.fake_pending(0)
+    log()
     ctx.close()
+    assert not [line for line in log() if line.startswith("bad")]
