@@ -1344,7 +1344,8 @@ void isaac_destroy(isaac_context* ctx) {
         if (r.dev) hipFree(r.dev);
         if (r.done) hipEventDestroy(r.done);
     }
-    for (auto& p : ctx->pending) hipEventDestroy(p.ev);
+    for (auto& p : ctx->pending)
+        if (p.pooled) hipEventDestroy(p.ev);      // the others are the ring's
     for (auto& t : ctx->timed) {
         hipEventDestroy(t.first);
         hipEventDestroy(t.second);
