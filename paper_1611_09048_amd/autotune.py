@@ -22,7 +22,7 @@ from . import binding
 
 WAVE_W = (1, 2, 4, 8, 16, 32, 64)
 WAVES_X = (1, 2, 4)
-UNROLL = (1, 2)
+UNROLL = (1,)              # 2 is accepted by the library and runs what 1 runs
 LANES = (1, 2, 4, 8, 16, 32, 64)
 MIN_WAVES = (0, 4)
 POOLED = (0, 1)
@@ -39,11 +39,12 @@ def candidates(unrolls: Sequence[int] = UNROLL, lanes: Sequence[int] = LANES, wa
                pooled: Sequence[int] = POOLED) -> List[Tuple]:
     """Valid (wave_w, waves_x, unroll, lanes_per_ray, min_waves, pooled) settings.
 
-    The pooled schedule ignores the tile shape, so it is tried once per lane count."""
+    The pooled schedule ignores the tile shape, so it is tried once per lane count;
+    one lane per ray runs the same kernel whatever min_waves, so it takes the first."""
     out = []
     for g in lanes:
         for u in (unrolls if g == 1 else (1,)):
-            for m in min_waves:
+            for m in (min_waves if g > 1 else min_waves[:1]):
                 if m and (g == 2 or g >= 32 or u == 2):
                     continue
                 if 0 in pooled:
