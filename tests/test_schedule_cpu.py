@@ -72,5 +72,19 @@ def test_lanes_of_iso_jobs(cpu, n, w, h, shape, want):
     volume(ctx, 0, n, OPAQUE)
     log()
     ctx.render([view(0, n, w, h, mode=binding.ISO, iso_values=[0.5])])
-    got = [int(m.group(1)) for m in [re.search(r"raycast_kernelILb0ELi(\d+)ELi0ELin[23]E", line) for line in log()] if m]
+    got = [int(m.group(1)) for m in [re.search(r"raycast_kernelILb0ELi(\d+)ELi\dELin[23]E", line) for line in log()] if m]
     assert got == [want]
+
+
+@pytest.mark.parametrize("guard,chain,want", [(1, "", "ELi0ELin3E"), (0, "", "ELi3ELin2E"), (1, "mul(2)", "ELi3ELin2E")])
+def test_iso_kernel_of_the_sources(cpu, guard, chain, want):
+    """Plain sources (FP32 scalars, guard layers, no chain) have a loop of 80 registers; the loop over any
+    sources is bound to the registers of 3 waves per SIMD."""
+    from paper_1611_09048_amd import binding
+    ctx, log = cpu
+    n = 24
+    ctx.set_sources(0, (n, n, n), [binding.source_desc(name="s", f_dim=1, dtype="f32", comp=[1 << 20], guard=guard,
+                                                      stride=(4, 4 * (n + 2), 4 * (n + 2) ** 2), chain=chain)])
+    log()
+    ctx.render([view(0, n, 128, 96, mode=binding.ISO, iso_values=[0.5])], binding.DIRECT)
+    assert [line for line in log() if "raycast_kernelILb0ELi8" + want in line]
