@@ -1343,16 +1343,23 @@ __device__ __forceinline__ int find_job(const DevJob* __restrict__ jobs, int n_j
     return lo;
 }
 
-// Pixel of this lane in tile t of job J (G lanes share one ray); false
-// outside the image.
+// First pixel of tile t of job J (G lanes share one ray), the same for the workgroup.
 template <int G>
-__device__ __forceinline__ bool pixel_of(const DevJob& J, int t, int lane, int wave, int& px, int& py) {
-    const int ray = lane / G;
-    const int ww = J.wave_w, wh = (64 / G) / ww;
-    const int gx = J.waves_x, gy = 4 / gx;
-    const int tx = t % J.tiles_x, ty = t / J.tiles_x;
-    px = J.cull[0] + tx * (ww * gx) + (wave % gx) * ww + ray % ww;
-    py = J.cull[1] + ty * (wh * gy) + (wave / gx) * wh + ray / ww;
+__device__ __forceinline__ void tile_origin(const DevJob& J, int t, int& x0, int& y0) {
+    const int ty = t / J.tiles_x, tx = t - ty * J.tiles_x;
+    x0 = __builtin_amdgcn_readfirstlane(J.cull[0] + tx * (J.wave_w * J.waves_x));
+    y0 = __builtin_amdgcn_readfirstlane(J.cull[1] + ty * ((64 / G) / J.wave_w * (4 / J.waves_x)));
+}
+
+// Pixel of a thread in the tile at (x0, y0); false outside the image.  The widths are
+// powers of two: shifts and masks, since every lane does this twice (as divisions it
+// was some 140 instructions a time, 3 us of a frame of 21 thousand waves).
+template <int G>
+__device__ __forceinline__ bool pixel_of(const DevJob& J, int x0, int y0, int thread, int& px, int& py) {
+    const int ray = (thread & 63) / G, wave = thread >> 6;
+    const int w = __builtin_ctz(J.wave_w), h = __builtin_ctz(64 / G) - w, x = __builtin_ctz(J.waves_x);
+    px = x0 + ((wave & (J.waves_x - 1)) << w) + (ray & (J.wave_w - 1));
+    py = y0 + ((wave >> x) << h) + (ray >> w);
     return px <= J.cull[2] && py <= J.cull[3];
 }
 
@@ -1406,7 +1413,7 @@ template <bool ORD, int G, int W, int SIGK>
 __global__ __launch_bounds__(kBlockThreads) __attribute__((amdgpu_waves_per_eu(W > 0 ? W : 1, 8)))
 void raycast_kernel(const DevJob* __restrict__ jobs, const float4* __restrict__ tf_pool, int n_jobs, int tile0) {
     extern __shared__ float4 s_tf[];
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const int lane = threadIdx.x & 63;
     const int tile = tile0 + (int)blockIdx.x;
     const DevJob& J = jobs[__builtin_amdgcn_readfirstlane(find_job(jobs, n_jobs, tile))];
     // Loops over adjacent values: the tables travel while the ray record does, whether a
@@ -1418,8 +1425,9 @@ void raycast_kernel(const DevJob* __restrict__ jobs, const float4* __restrict__ 
     StagedTables tab;
     if constexpr (kEarly) tab = load_tables(J, tf_pool);
     // tiles cover the box's screen rectangle only (the fill kernel clears the rest)
-    int px = 0, py = 0;
-    const bool in_image = pixel_of<G>(J, tile - J.tile_begin, lane, wave, px, py);
+    int x0, y0, px, py;
+    tile_origin<G>(J, tile - J.tile_begin, x0, y0);
+    const bool in_image = pixel_of<G>(J, x0, y0, (int)threadIdx.x, px, py);
     RaySetup R;
     bool hit;
     if (J.rays) {
@@ -1470,7 +1478,7 @@ void raycast_kernel(const DevJob* __restrict__ jobs, const float4* __restrict__ 
     // through the loop above
     int tid = (int)threadIdx.x;
     asm("" : "+v"(tid));
-    if (pixel_of<G>(J, tile - J.tile_begin, tid & 63, tid >> 6, px, py) && (tid & (G - 1)) == 0) {
+    if (pixel_of<G>(J, x0, y0, tid, px, py) && (tid & (G - 1)) == 0) {
         const size_t pix = (size_t)py * J.width + px;
         reinterpret_cast<float4*>(J.out)[pix] = c;
         if (J.out_samples) J.out_samples[pix] = count;
