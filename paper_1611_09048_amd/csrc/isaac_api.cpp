@@ -926,7 +926,7 @@ isaac_status enqueue_jobs(isaac_context* ctx, const isaac_render_desc* jobs, con
 // FP32 value per source.  The values are the ones the loop would compute, so
 // the image does not change.
 isaac_status derive_volumes(isaac_context* ctx, const isaac_render_desc* jobs, std::vector<DevJob>& djs, bool force,
-                            hipStream_t stream) {
+                            hipStream_t stream, bool freeze = false) {
     const int n = (int)djs.size();
     std::vector<int> vols;
     for (int i = 0; i < n; ++i)
@@ -959,9 +959,9 @@ isaac_status derive_volumes(isaac_context* ctx, const isaac_render_desc* jobs, s
         // trilinear volume jobs over sources without guard layers: a derived guard layer
         // that repeats the border values makes the loop's border clamp unnecessary (where
         // it fits the size limit below; + 3: the pairs' rounding)
-        if (g == 0 && clamps &&
-            16.0 * (v.dims[0] + 3.0) * (v.dims[1] + 3.0) * (v.dims[2] + 3.0) < (double)((int64_t)1 << 31))
-            g = 1;
+        const bool layer = g == 0 && clamps &&
+            16.0 * (v.dims[0] + 3.0) * (v.dims[1] + 3.0) * (v.dims[2] + 3.0) < (double)((int64_t)1 << 31);
+        if (layer) g = 1;
         const int64_t ex = v.dims[0] + 2 * g, ey = v.dims[1] + 2 * g, ez = v.dims[2] + 2 * g;
         // The derived sources in either layout: x fastest, or (three sources) the (y, z)
         // pairs, stored y and z shifted by gp, an even number of layers at least g, so
@@ -1016,8 +1016,11 @@ isaac_status derive_volumes(isaac_context* ctx, const isaac_render_desc* jobs, s
         };
         // The paired layout only when every job of the volume in this call then runs the
         // three-source loop, its only reader (calls with iso or fewer-source jobs keep x
-        // fastest; a volume frozen in pairs is read directly by such jobs later).
-        bool paired = nd == 3;
+        // fastest; a volume frozen in pairs is read directly by such jobs later).  Sources
+        // without guard layers freeze x fastest, since in place such jobs clamp at every
+        // corner (FP16 fields of 128^3 at 1024 x 768, us a call in pairs and x fastest: one
+        // of three 325 and 132, two 455 and 214, iso 172 and 63, all three 85 and 92).
+        bool paired = nd == 3 && !(freeze && layer);
         if (paired) {
             const Layout P = layout_of(true);
             for (int i = 0; i < n && paired; ++i) {
@@ -1573,7 +1576,7 @@ isaac_status isaac_freeze_volume(isaac_context* ctx, int volume_id) {
     if (st) return st;
     st = prepare_sources(ctx, &d, 1, true);
     if (st) return st;
-    st = derive_volumes(ctx, &d, djs, true, ctx->stream);
+    st = derive_volumes(ctx, &d, djs, true, ctx->stream, true);
     if (st) return st;
     HIP_TRY(ctx, hipStreamSynchronize(ctx->stream));
     const DevJob& dj = djs[0];
