@@ -233,30 +233,33 @@ void set_cull_rect(DevJob& dj) {
     dj.cull[3] = (int)clampd(std::ceil(ymax) + 1.0, -1.0, (double)dj.height - 1);
 }
 
-// A group gains where a lane alone would wait on many gathers one after another, and
-// loses where most of a row lies past the ray's end or its termination and the rays
-// fill the chip without it.  The lines lie where the times cross on 400 single calls
-// (256 x 256 to 3840 x 2160, volumes of 16^3 to 160^3, one to four sources, opacities of
-// 0.015 to 1) and 100 batches, on the side of the groups, whose gain is the larger.  us a
-// call with 1, 4 and 16 lanes, by rays and points: 6.7 K rays, 77 points 98, 41, 25; 27 K,
-// 1 point (in place) 22.5, 24.6, 33.9, 77 points 88, 43, 32; 61 K, 1 point 21.2, 22.4,
-// 30.8, 77 points (three sources) 140, 71, 67; 120 K, 1 point 25, 28, 44, 3 points 33,
-// 36, 55, 20 points 40, 34, 49, 177 points 303, 183, 180; 480 K, 1 point 46, 57, 115, 10
-// points 57, 69, 129, 39 points (three sources) 176, 148, 198, 191 points 662, 429, 475; a
-// batch of 135 K rays in place, 83 points 2250, 853, 601; one of 670 K, 58 points 371,
-// 218, 321.
-int lanes_in_order(double rays, double points) {
-    if (rays > 27000.0 * points) return 1;
-    return rays < 190000.0 && rays <= 2600.0 * points ? 16 : 4;
+// A group gains where a lane alone would wait on many gathers one after another and the
+// rays are too few to fill the chip with a lane each.  It loses where most of a row lies
+// past the ray's end or its termination, and, once the chip is full, where the rays are
+// closer together than their points: then a wave of one lane per ray reads fewer cache
+// lines.  The lines are drawn so that no call is slower than with one lane: on 1020 calls
+// drawn at random (160 to 3840 pixels wide, 1 to 30 jobs, volumes of 14^3 to 200^3, one to
+// four sources derived and in place, steps of 0.25 to 4, from inside the volume to four
+// diagonals away, opacities of 0.015 to 1), 9 are more than 5 % slower, and all together
+// take 0.66 of the time, 1.3 % above the best of the three for each.  us a call with 1, 4
+// and 16 lanes, by rays, points and spread: 6.7 K, 77, 1.2: 98, 41, 25; 61 K, 1, 5: 21, 22, 31;
+// 61 K, 77, 5 (three sources): 140, 71, 67; 120 K, 1, 7: 25, 28, 44; 135 K in 20 jobs in
+// place, 83, 1: 2250, 853, 601; 480 K, 191, 3.4: 662, 429, 475; 400 K, 270, 3.7 (three): 574, 747,
+// 769; 830 K, 49, 90 (step 4): 93, 162, 197.
+int lanes_in_order(const RayLoad& l) {
+    if (l.rays > 20000.0 * l.points) return 1;
+    if ((l.rays > 100000.0 && l.spread > 6.0) || (l.rays > 300000.0 && l.spread > 3.5)) return 1;
+    return l.rays < 120000.0 && l.rays <= 1800.0 * l.points && !(l.rays > 40000.0 && l.spread > 6.0) ? 16 : 4;
 }
 
 // Eight lanes find a crossing in an eighth of the dependent steps, and evaluate up to 7
-// points beyond it: many rays of few points fill the chip without them.  us a call
-// with 1 and 8 lanes, surfaces in the middle of the volume and none at all: 120 K rays,
-// 19 points 71, 57 and 96, 76; 480 K rays, 19 points 109, 142 and 154, 199, 39 points
-// 100, 145 and 295, 336, 77 points 117, 148 and 772, 631, 191 points 163, 179 and 2642,
-// 1717.
-int lanes_iso(double rays, double points) { return rays >= 283000.0 && points < 100.0 ? 1 : 8; }
+// points beyond it: on 660 calls drawn as above, surfaces near and far or none, 3 are more
+// than 5 % slower than with one lane, and all together take 0.64 of the time.  us a call
+// with 1 and 8 lanes: 6.7 K rays, 191 points 2550, 343; 120 K, 39 points 140, 88; 480 K, 39
+// points 100, 145; 1.4 M, 105 points 960, 1870; 3.8 M, 153 points 629, 1780.
+int lanes_iso(const RayLoad& l) {
+    return l.rays > 6000.0 * l.points || l.rays > 283000.0 || (l.rays > 160000.0 && l.spread > 8.0) ? 1 : 8;
+}
 
 }  // namespace host
 }  // namespace isaac

@@ -41,14 +41,21 @@ bool camera_basis(const isaac_render_desc& j, CameraBasis& cb, std::string& err)
 // the eye plane.
 void set_cull_rect(DevJob& dj);
 
-// Lanes that evaluate a ray of the one-lane schedule in a launch of `rays` rays that
-// take `points` scan points each, about: 1, or a group of 4 or 16 whose points are
-// composited in order.  Every choice gives the same image.
-int lanes_in_order(double rays, double points);
+// What the rays of a launch are expected to be like.
+struct RayLoad {
+    double rays = 0.0;      // that meet their boxes
+    double points = 0.0;    // scan points of each, to its end or its termination
+    double spread = 0.0;    // pixels per voxel, times twice the step where that is more than one voxel:
+                            // how much further apart a ray's own points lie than its neighbours'
+};
+
+// Lanes that evaluate a ray of the one-lane schedule: 1, or a group of 4 or 16 whose
+// points are composited in order.  Every choice gives the same image.
+int lanes_in_order(const RayLoad& l);
 
 // Lanes per ray of iso-surface jobs whose schedule does not ask for 8 or more: 1 or 8,
 // for the same image.
-int lanes_iso(double rays, double points);
+int lanes_iso(const RayLoad& l);
 
 }  // namespace host
 }  // namespace isaac

@@ -35,6 +35,7 @@ using isaac::host::compile_chain;
 using isaac::host::CompiledChain;
 using isaac::host::lanes_in_order;
 using isaac::host::lanes_iso;
+using isaac::host::RayLoad;
 using isaac::host::set_cull_rect;
 
 namespace {
@@ -712,11 +713,12 @@ size_t rect_pixels(const DevJob& dj) {
     return (size_t)std::max(0, dj.cull[2] - dj.cull[0] + 1) * std::max(0, dj.cull[3] - dj.cull[1] + 1);
 }
 
-// Rays of the job expected to meet its box (the box's shadow along the line of sight to
-// its centre, at most the screen rectangle), and the scan points such a ray is expected
-// to take, to the box's end or to its termination as if the sources' values were spread
-// evenly over their tables.
-void expected_rays(const isaac_context* ctx, const DevJob& dj, double& rays, double& points) {
+// What the job's rays are expected to be like: those that meet its box (the box's shadow
+// along the line of sight to its centre, at most the screen rectangle), and their
+// points, to the box's end or to termination as if the sources' values were spread evenly
+// over their tables.
+RayLoad expected_rays(const isaac_context* ctx, const DevJob& dj) {
+    RayLoad l;
     double d[3], r = 0.0, diag = 0.0, shadow = 0.0, opacity = 0.0;
     for (int a = 0; a < 3; ++a) {
         d[a] = dj.ortho ? dj.fwd[a] : dj.org[a] + 0.5 * dj.dims[a] - dj.eye[a];
@@ -724,14 +726,16 @@ void expected_rays(const isaac_context* ctx, const DevJob& dj, double& rays, dou
         diag += (double)dj.dims[a] * dj.dims[a];
     }
     const double cells = (double)dj.dims[0] * dj.dims[1] * dj.dims[2], samples = estimate_samples(dj);
+    const double cell_pixels = samples / cells * dj.step;      // pixels per cell cross-section
     for (int a = 0; a < 3; ++a) shadow += std::abs(d[a]) / std::sqrt(std::max(r, 1e-12)) * cells / dj.dims[a];
-    // (samples / cells * step: pixels per cell cross-section)
-    rays = std::min((double)rect_pixels(dj), shadow * (samples / cells * dj.step));
-    points = rays > 0.0 ? std::min(samples / rays, std::sqrt(diag) / dj.step) : 0.0;
+    l.rays = std::min((double)rect_pixels(dj), shadow * cell_pixels);
+    l.points = l.rays > 0.0 ? std::min(samples / l.rays, std::sqrt(diag) / dj.step) : 0.0;
+    l.spread = std::sqrt(cell_pixels) * std::max(1.0, 2.0 * dj.step);
     for (int s = 0; s < dj.n_src; ++s) opacity += dj.src[s].weight * ctx->tf_slots[dj.src[s].tf_slot].opacity;
-    if (dj.mode == ISAAC_ISO || dj.ert > 1.f || opacity <= 0.0) return;
-    const double left = std::max(1.0 - dj.ert, 1e-7);      // transparency at which the ray ends
-    points = std::min(points, std::max(1.0, std::log(left) / std::log(1.0 - std::min(opacity, 0.999))));
+    if (dj.mode == ISAAC_ISO || dj.ert > 1.f || opacity <= 0.0) return l;
+    const double left = std::max(1.0 - dj.ert, 1e-7);          // transparency at which the ray ends
+    l.points = std::min(l.points, std::max(1.0, std::log(left) / std::log(1.0 - std::min(opacity, 0.999))));
+    return l;
 }
 
 // noalloc: the call may not allocate: the set-up pass writes its ray records
@@ -747,15 +751,15 @@ isaac_status enqueue_jobs(isaac_context* ctx, const isaac_render_desc* jobs, con
     int lanes = djs[0].lanes, hint = djs[0].waves_hint;
     const bool ordered = lanes == 1 && djs[0].mode != ISAAC_ISO;
     if (lanes == 1) {
-        double rays = 0.0, points = 0.0;
+        RayLoad all;
         for (const DevJob& dj : djs) {
-            double n, p;
-            expected_rays(ctx, dj, n, p);
-            rays += n;
-            points += n * p;
+            const RayLoad l = expected_rays(ctx, dj);
+            all.rays += l.rays;
+            all.points += l.rays * l.points;
+            all.spread += l.rays * l.spread;
         }
-        points = rays > 0.0 ? points / rays : 0.0;
-        lanes = ordered ? lanes_in_order(rays, points) : lanes_iso(rays, points);
+        if (all.rays > 0.0) all.points /= all.rays, all.spread /= all.rays;
+        lanes = ordered ? lanes_in_order(all) : lanes_iso(all);
     }
     int tiles = 0;
     for (int i = 0; i < n; ++i) {

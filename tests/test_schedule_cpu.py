@@ -34,7 +34,7 @@ def lanes(log):
 @pytest.mark.parametrize("n,w,h,alpha,ert,want", [
     (64, 256, 256, THIN, 0, 16), (160, 1024, 768, THIN, 0, 16), (160, 3840, 2160, THIN, 0, 4),
     (64, 1920, 1080, HALF, 0, 4), (64, 1920, 1080, OPAQUE, 0, 1), (64, 3840, 2160, HALF, 0, 1),
-    (160, 3840, 2160, OPAQUE, 0, 1), (160, 512, 512, OPAQUE, 0, 1), (16, 3840, 2160, THIN, 0, 4),
+    (160, 3840, 2160, OPAQUE, 0, 1), (160, 512, 512, OPAQUE, 0, 1), (16, 3840, 2160, THIN, 0, 1),
     (16, 512, 512, THIN, 0, 16), (160, 3840, 2160, OPAQUE, 2.0, 4), (160, 1024, 768, OPAQUE, 2.0, 16),
     (160, 1920, 1080, THIN, 0.01, 1)])
 def test_lanes_follow_rays_and_points(cpu, n, w, h, alpha, ert, want):
@@ -42,6 +42,21 @@ def test_lanes_follow_rays_and_points(cpu, n, w, h, alpha, ert, want):
     volume(ctx, 0, n, alpha)
     log()
     ctx.render([view(0, n, w, h, ert_threshold=ert)])
+    assert lanes(log) == [want]
+
+
+@pytest.mark.parametrize("factor,step,w,want", [
+    (1.0, 0.5, 400, 16), (0.4, 0.5, 700, 1), (1.0, 4.0, 700, 1), (0.4, 0.5, 190, 16), (0.4, 4.0, 240, 4)])
+def test_close_views_and_long_steps(cpu, factor, step, w, want):
+    """Where the rays are closer together than their points, and fill the chip, one lane reads fewer lines."""
+    from paper_1611_09048_amd import binding
+    ctx, log = cpu
+    n = 64
+    volume(ctx, 0, n, THIN)
+    log()
+    d, c = factor * n * 3 ** 0.5, n / 2
+    ctx.render([binding.render_desc(volume_id=0, width=w, height=w, eye=(c + d * 0.7, c + d * 0.57, c + d * 0.43),
+                                    center=(c, c, c), up=(0, 0, 1), out_rgba=1 << 30, interpolation=1, step=step)])
     assert lanes(log) == [want]
 
 
@@ -62,8 +77,8 @@ def test_a_batch_is_one_launch_and_an_empty_rectangle_counts_nothing(cpu):
 
 
 @pytest.mark.parametrize("n,w,h,shape,want", [
-    (64, 256, 256, 1, 8), (16, 1920, 1080, 1, 8), (16, 3840, 2160, 1, 1), (32, 3840, 2160, 4, 1),
-    (160, 3840, 2160, 1, 8), (16, 3840, 2160, 16, 8)])
+    (64, 256, 256, 1, 8), (64, 1920, 1080, 4, 8), (16, 3840, 2160, 1, 1), (32, 3840, 2160, 4, 1),
+    (160, 3840, 2160, 1, 1), (16, 3840, 2160, 16, 8)])
 def test_lanes_of_iso_jobs(cpu, n, w, h, shape, want):
     from paper_1611_09048_amd import binding
     ctx, log = cpu
