@@ -256,9 +256,12 @@ int lanes_in_order(const RayLoad& l) {
 // points beyond it: on 660 calls drawn as above, surfaces near and far or none, 3 are more
 // than 5 % slower than with one lane, and all together take 0.64 of the time.  us a call
 // with 1 and 8 lanes: 6.7 K rays, 191 points 2550, 343; 120 K, 39 points 140, 88; 480 K, 39
-// points 100, 145; 1.4 M, 105 points 960, 1870; 3.8 M, 153 points 629, 1780.
+// points 100, 145; 1.4 M, 105 points 960, 1870; 3.8 M, 153 points 629, 1780.  From afar
+// (spread 1.3, as batches of small images are) the rays of a wave lie far apart, and 8
+// lanes stay the faster: 64 images, 430 K rays, 57 points 324, 198.
 int lanes_iso(const RayLoad& l) {
-    return l.rays > 6000.0 * l.points || l.rays > 283000.0 || (l.rays > 160000.0 && l.spread > 8.0) ? 1 : 8;
+    const bool full = l.rays > 6000.0 * l.points || l.rays > 283000.0 || (l.rays > 160000.0 && l.spread > 8.0);
+    return full && l.spread > 1.6 ? 1 : 8;
 }
 
 }  // namespace host

@@ -91,6 +91,17 @@ def test_lanes_of_iso_jobs(cpu, n, w, h, shape, want):
     assert got == [want]
 
 
+def test_iso_batch_of_small_images(cpu):
+    """Rays far apart (1.3 pixels a voxel): 8 lanes, however many they are."""
+    from paper_1611_09048_amd import binding
+    ctx, log = cpu
+    volume(ctx, 0, 48, OPAQUE)
+    log()
+    ctx.render([view(0, 48, 256, 256, mode=binding.ISO, iso_values=[0.5]) for _ in range(64)])
+    got = [int(m.group(1)) for m in [re.search(r"raycast_kernelILb0ELi(\d+)ELi\dELin[23]E", line) for line in log()] if m]
+    assert got == [8]
+
+
 @pytest.mark.parametrize("guard,chain,want", [(1, "", "ELi0ELin3E"), (0, "", "ELi3ELin2E"), (1, "mul(2)", "ELi3ELin2E")])
 def test_iso_kernel_of_the_sources(cpu, guard, chain, want):
     """Plain sources (FP32 scalars, guard layers, no chain) have a loop of 80 registers; the loop over any
