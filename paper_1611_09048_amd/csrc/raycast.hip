@@ -1415,7 +1415,8 @@ void raycast_kernel(const DevJob* __restrict__ jobs, const float4* __restrict__ 
     extern __shared__ float4 s_tf[];
     const int lane = threadIdx.x & 63;
     const int tile = tile0 + (int)blockIdx.x;
-    const DevJob& J = jobs[__builtin_amdgcn_readfirstlane(find_job(jobs, n_jobs, tile))];
+    const int job = __builtin_amdgcn_readfirstlane(find_job(jobs, n_jobs, tile));
+    const DevJob& J = jobs[job];
     // Loops over adjacent values: the tables travel while the ray record does, whether a
     // ray of the tile meets the box or not, so a workgroup waits for memory once before
     // its rows, not for the record, then for the tables (a wave lives 8.6 us on the
@@ -1426,7 +1427,7 @@ void raycast_kernel(const DevJob* __restrict__ jobs, const float4* __restrict__ 
     if constexpr (kEarly) tab = load_tables(J, tf_pool);
     // tiles cover the box's screen rectangle only (the fill kernel clears the rest)
     int x0, y0, px, py;
-    tile_origin<G>(J, tile - J.tile_begin, x0, y0);
+    tile_origin<G>(J, job_tile(tile - J.tile_begin, job, J.tiles_x * J.tiles_y), x0, y0);
     const bool in_image = pixel_of<G>(J, x0, y0, (int)threadIdx.x, px, py);
     RaySetup R;
     bool hit;
