@@ -249,7 +249,8 @@ void set_cull_rect(DevJob& dj) {
 int lanes_in_order(const RayLoad& l) {
     if (l.rays > 20000.0 * l.points) return 1;
     if ((l.rays > 100000.0 && l.spread > 6.0) || (l.rays > 300000.0 && l.spread > 3.5)) return 1;
-    return l.rays < 120000.0 && l.rays <= 1800.0 * l.points && !(l.rays > 40000.0 && l.spread > 6.0) ? 16 : 4;
+    const bool few = l.rays < (l.spread < 2.0 ? 260000.0 : l.spread > 6.0 ? 40000.0 : 120000.0);
+    return few && l.rays <= 1800.0 * l.points ? 16 : 4;
 }
 
 // Eight lanes find a crossing in an eighth of the dependent steps, and evaluate up to 7

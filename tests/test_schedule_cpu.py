@@ -74,6 +74,10 @@ def test_a_batch_is_one_launch_and_an_empty_rectangle_counts_nothing(cpu):
     assert lanes(log) == [1]
     ctx.render([view(0, 64, 512, 512), view(1, 160, 512, 512)])
     assert lanes(log) == [16]
+    volume(ctx, 2, 90, THIN)
+    log()
+    ctx.render([view(2, 90, 256, 256) for _ in range(26)])         # 180 thousand rays, 0.7 pixels a voxel
+    assert lanes(log) == [16]
 
 
 @pytest.mark.parametrize("n,w,h,shape,want", [
