@@ -2293,6 +2293,15 @@ DeriveFn derive_variant(const DeriveArgs& a, int sig) {
         default: return derive_general<3, true>(dim);
         }
     }
+    // x fastest: the compiled kinds for three sources too, whose pass is shorter where a
+    // launch is (100 volumes of 24^3, iso: 898 us a call by the general pass, 770; from 96^3 on
+    // they take the same time)
+    switch (a.n == 3 ? sig : (int)SIG_GENERIC) {
+    case SIG_PIC3_F32: return derive_kernel<SIG_PIC3_F32, 3, 3, false>;
+    case SIG_PIC3_F16: return derive_kernel<SIG_PIC3_F16, 3, 3, false>;
+    case SIG_PIC3_BF16: return derive_kernel<SIG_PIC3_BF16, 3, 3, false>;
+    default: break;
+    }
     switch (a.n) {
     case 1: return derive_general<1, false>(dim);
     case 2: return derive_general<2, false>(dim);
