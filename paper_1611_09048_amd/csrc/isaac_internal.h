@@ -136,7 +136,7 @@ struct LaunchArgs {
     int total_tiles;
     const float* tf_pool;      // device, [slot][256][4]
     int max_src;               // widest job's active source count (sizes the LDS tables)
-    int ordered;               // 1: jobs of one lane per ray, evaluated by groups of `lanes` (4 or 16) lanes
+    int ordered;               // 1: jobs of one lane per ray, evaluated by `lanes` (1, 4 or 16) lanes each
     int lanes;                 // lanes per ray (kernel variant)
     int waves_hint;            // 1: the variant compiled for at least 4 waves per SIMD
     int sig;                   // the jobs' common Signature, or -1 when they differ

@@ -1079,11 +1079,6 @@ __device__ __forceinline__ void group_scan(int lane, float& c0, float& c1, float
     }
 }
 
-// One row of G scan points of a ray composited into acc.  A lane past the ray's
-// last scan point (valid false) may carry any finite values (the callers give it
-// the last point's sample): the scan is inclusive, so no kept lane's prefix
-// depends on it, the termination ballot masks it, and the lane taken is never
-// past the row's last kept point.
 // The lane index, opaque to the optimizer: masks and permute addresses made from
 // it inside a loop are recomputed there (one instruction each) instead of held in
 // registers through it.  k0 (the loop's) keeps it in the loop; volatile would too, but
@@ -1094,6 +1089,11 @@ __device__ __forceinline__ int fresh(int lane, int k0) {
     return lane;
 }
 
+// One row of G scan points of a ray composited into acc.  A lane past the ray's
+// last scan point (valid false) may carry any finite values (the callers give it
+// the last point's sample): the scan is inclusive, so no kept lane's prefix
+// depends on it, the termination ballot masks it, and the lane taken is never
+// past the row's last kept point.
 template <int G>
 __device__ __forceinline__ bool row_composite(const DevJob& J, const RaySetup& R, int lane, int k0, bool valid,
                                               float c0, float c1, float c2, float a, RayAccum& acc) {
@@ -1402,9 +1402,9 @@ __device__ __forceinline__ void store_tables(const DevJob& J, const float4* __re
 // Waves-per-SIMD hint: W = 0 leaves register allocation to the compiler and
 // issues every load of a scan point at once; W > 0 asks for at least W
 // resident waves per SIMD and evaluates the sources one after another.  The
-// loops over up to three adjacent values need no bound: they fit the 64 vector
-// registers of 8 waves, since what a row needs of the lane index is made afresh
-// (fresh()) and the pixel is not kept through the loop.
+// pipelined loop over one adjacent value and, bound, the loop over three fit the 64
+// vector registers of 8 waves, since what a row needs of the lane index is made
+// afresh (fresh()) and the pixel is not kept through the loop.
 // SIGK >= 0: the kernel runs only that source signature (every job of the
 // launch has it); SIGK = -1: it dispatches on each job's signature; SIGK = -2:
 // iso-surface jobs; SIGK = -3: iso-surface jobs whose sources are all plain
@@ -2069,13 +2069,14 @@ __global__ __launch_bounds__(256) void strided_copy_kernel(CopyArgs a) {
 using KernelFn = void (*)(const DevJob*, const float4*, int, int);
 
 // The variant (W) of a signature's loop under the hint for at least 4 waves per
-// SIMD.  One or two adjacent values: the pipelined loop (54 and 74 vector
+// SIMD.  One or two adjacent values: the pipelined loop (60 and 78 vector
 // registers, 8 and 6 waves) is the faster one (two derived sources at 720p 81
 // against 88 us a call, a 48^3 scalar 20.7 against 22.4).  Scalar and vectors read
-// in place: every source's loads together (104 registers, 4 waves) instead of a
+// in place: every source's loads together (105 to 113 registers, 4 waves) instead of a
 // source after the other: 272 against 350 us for 192^3 FP32 at 1024 x 768.  Three
-// and four adjacent values keep the loop with more waves (six served requests 587
-// against 613 us, four derived sources 76 against 79), the general loop its bound.
+// and four adjacent values keep the loop with more waves (62 and 76 registers, 8 and 6
+// waves, against 90 and 104, 5 and 4, pipelined: six served requests 587 against 613 us,
+// four derived sources 76 against 79), the general loop its bound.
 template <int SIGK>
 constexpr int kHintW = Il<SIGK>::n >= 3 || SIGK == SIG_GENERIC ? 4 : 0;
 
@@ -2192,6 +2193,10 @@ PoolFn pick_pool_kernel(int sig, int lanes, int hint) {
     case SIG_IL3P: return pick_pool_specialized<SIG_IL3P>(lanes, hint);
     case SIG_GENERIC: return pick_pool_specialized<SIG_GENERIC>(lanes, hint);
     case SIG_IL1: return pick_pool_specialized<SIG_IL1>(lanes, hint);
+    // SIG_IL1C, SIG_IL2 and SIG_IL4 run the dispatching kernel: its 132 registers keep 3 waves
+    // per SIMD instead of 7 or 8, and fewer resident rays at a time take less time here (160^3 at
+    // 1280 x 720, 16 lanes, dispatching and own kernel, us a call: a guard-less scalar 194 and
+    // 234, two derived sources 218 and 261, four 237 and 269; with 2 lanes 505 and 501)
     default: break;
     }
     switch (lanes) {
