@@ -122,7 +122,6 @@ struct DevJob {
     DevSource src[kMaxSources];
 };
 
-// Launch entry points implemented in raycast.hip.
 // The tile of a job's image (of n) that the job's workgroup t renders.  Workgroups go to
 // the 8 XCDs by turns: in a batch of images of 8, 16, ... tiles each, a place in the
 // image, and with it the long rays of every image's middle, would fall to the same XCDs
@@ -130,6 +129,7 @@ struct DevJob {
 // in place, iso, one lane per ray: 540 -> 329 us a call).
 constexpr int job_tile(int t, int job, int n) { return job == 0 ? t : (t + job % n) % n; }
 
+// Launch entry points implemented in raycast.hip.
 struct LaunchArgs {
     const DevJob* jobs;        // device
     int n_jobs;
