@@ -47,6 +47,8 @@ struct RayLoad {
     double points = 0.0;    // scan points of each, to its end or its termination
     double spread = 0.0;    // pixels per voxel, times twice the step where that is more than one voxel:
                             // how much further apart a ray's own points lie than its neighbours'
+    double pixels = 0.0;    // per voxel at the volume's centre
+    double rows = 0.0;      // rows of voxels (y or z) between two scan points of a ray
 };
 
 // Lanes that evaluate a ray of the one-lane schedule: 1, or a group of 4 or 16 whose
@@ -56,6 +58,11 @@ int lanes_in_order(const RayLoad& l);
 // Lanes per ray of iso-surface jobs whose schedule does not ask for 8 or more: 1 or 8,
 // for the same image.
 int lanes_iso(const RayLoad& l);
+
+// Whether a trilinear point of a scalar whose x neighbours are adjacent takes its eight
+// corners one by one rather than in pairs, where `lanes` lanes share a ray: the same image.
+// clamp: at a border the corners are clamped (no guard layers).
+bool corners_one_by_one(const RayLoad& l, int lanes, bool clamp);
 
 }  // namespace host
 }  // namespace isaac

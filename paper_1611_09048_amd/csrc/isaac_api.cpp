@@ -33,6 +33,7 @@ using isaac::host::camera_basis;
 using isaac::host::CameraBasis;
 using isaac::host::compile_chain;
 using isaac::host::CompiledChain;
+using isaac::host::corners_one_by_one;
 using isaac::host::lanes_in_order;
 using isaac::host::lanes_iso;
 using isaac::host::RayLoad;
@@ -730,12 +731,30 @@ RayLoad expected_rays(const isaac_context* ctx, const DevJob& dj) {
     for (int a = 0; a < 3; ++a) shadow += std::abs(d[a]) / std::sqrt(std::max(r, 1e-12)) * cells / dj.dims[a];
     l.rays = std::min((double)rect_pixels(dj), shadow * cell_pixels);
     l.points = l.rays > 0.0 ? std::min(samples / l.rays, std::sqrt(diag) / dj.step) : 0.0;
-    l.spread = std::sqrt(cell_pixels) * std::max(1.0, 2.0 * dj.step);
+    l.pixels = std::sqrt(cell_pixels);
+    l.spread = l.pixels * std::max(1.0, 2.0 * dj.step);
+    l.rows = dj.step * (std::abs(d[1]) + std::abs(d[2])) / std::sqrt(std::max(r, 1e-12));
     for (int s = 0; s < dj.n_src; ++s) opacity += dj.src[s].weight * ctx->tf_slots[dj.src[s].tf_slot].opacity;
     if (dj.mode == ISAAC_ISO || dj.ert > 1.f || opacity <= 0.0) return l;
     const double left = std::max(1.0 - dj.ert, 1e-7);          // transparency at which the ray ends
     l.points = std::min(l.points, std::max(1.0, std::log(left) / std::log(1.0 - std::min(opacity, 0.999))));
     return l;
+}
+
+// The rays of a launch's jobs together.
+RayLoad expected_rays(const isaac_context* ctx, const std::vector<DevJob>& djs) {
+    RayLoad all;
+    for (const DevJob& dj : djs) {
+        const RayLoad l = expected_rays(ctx, dj);
+        all.rays += l.rays;
+        all.points += l.rays * l.points;
+        all.spread += l.rays * l.spread;
+        all.pixels += l.rays * l.pixels;
+        all.rows += l.rays * l.rows;
+    }
+    if (all.rays > 0.0)
+        all.points /= all.rays, all.spread /= all.rays, all.pixels /= all.rays, all.rows /= all.rays;
+    return all;
 }
 
 // noalloc: the call may not allocate: the set-up pass writes its ray records
@@ -751,14 +770,7 @@ isaac_status enqueue_jobs(isaac_context* ctx, const isaac_render_desc* jobs, con
     int lanes = djs[0].lanes, hint = djs[0].waves_hint;
     const bool ordered = lanes == 1 && djs[0].mode != ISAAC_ISO;
     if (lanes == 1) {
-        RayLoad all;
-        for (const DevJob& dj : djs) {
-            const RayLoad l = expected_rays(ctx, dj);
-            all.rays += l.rays;
-            all.points += l.rays * l.points;
-            all.spread += l.rays * l.spread;
-        }
-        if (all.rays > 0.0) all.points /= all.rays, all.spread /= all.rays;
+        const RayLoad all = expected_rays(ctx, djs);
         lanes = ordered ? lanes_in_order(all) : lanes_iso(all);
     }
     int tiles = 0;
@@ -788,7 +800,10 @@ isaac_status enqueue_jobs(isaac_context* ctx, const isaac_render_desc* jobs, con
     for (const DevJob& dj : djs) scalars = scalars && scalar(dj.sig);
     for (const DevJob& dj : djs)
         if (dj.sig != la.sig) la.sig = scalars ? (int)SIG_F32x1 : -1;
-    // FP32 scalars of different forms in one launch: the loop that takes any of them
+    bool pairs = scalars && !ordered && (lanes == 4 || lanes == 8) && !(n == 1 && djs[0].pool);
+    for (const DevJob& dj : djs) pairs = pairs && dj.interp && dj.mode != ISAAC_ISO;
+    if (pairs && corners_one_by_one(expected_rays(ctx, djs), lanes, la.sig == SIG_IL1C)) la.sig = SIG_F32x1;
+    // FP32 scalars of different forms, or by single corners: the loop that takes any of them
     // (the dispatching kernel keeps 3 waves per SIMD, that loop 8)
     if (scalars && la.sig == SIG_F32x1)
         for (int i = 0; i < n; ++i) r->host[i].sig = SIG_F32x1;
