@@ -1566,8 +1566,12 @@ void raycast_pool_kernel(const DevJob* __restrict__ jobs, const float4* __restri
     const int n_rays = __builtin_amdgcn_readfirstlane(counters[0]);   // the setup kernel's count
     const int lane = (int)(threadIdx.x & 63);
     const int leader = lane & ~(G - 1);
-    constexpr int kChunk = 2 * (64 / G);                                 // rays taken per atomic
-    int q_next = 0, q_end = 0;                                           // the wave's local queue
+    constexpr int kChunk = 2 * (64 / G);                                 // rays taken at a time
+    // the wave's local queue, at first the chunk of its own number; the atomics of all waves on
+    // one counter take about 14 ns each, one after another (7168 waves: 100 us)
+    const int wave = (int)blockIdx.x * (kBlockThreads / 64) + (int)(threadIdx.x >> 6);
+    const int handed = (int)gridDim.x * (kBlockThreads / 64) * kChunk;
+    int q_next = min(__builtin_amdgcn_readfirstlane(wave) * kChunk, n_rays), q_end = min(q_next + kChunk, n_rays);
     bool exhausted = false, live = false;
     RaySetup R;
     int pixel = 0, k0 = 0;
@@ -1577,9 +1581,11 @@ void raycast_pool_kernel(const DevJob* __restrict__ jobs, const float4* __restri
         unsigned long long idle = __ballot(!live && lane == leader);
         while (idle && !exhausted) {
             if (q_next >= q_end) {
-                int base = 0;
-                if (lane == 0) base = atomicAdd(&counters[1], kChunk);
-                base = __shfl(base, 0);
+                int base = handed;
+                if (handed < n_rays) {
+                    if (lane == 0) base += atomicAdd(&counters[1], kChunk);
+                    base = __shfl(base, 0);
+                }
                 if (base >= n_rays) {
                     exhausted = true;
                     break;
