@@ -2199,10 +2199,12 @@ PoolFn pick_pool_kernel(int sig, int lanes, int hint) {
     case SIG_IL3P: return pick_pool_specialized<SIG_IL3P>(lanes, hint);
     case SIG_GENERIC: return pick_pool_specialized<SIG_GENERIC>(lanes, hint);
     case SIG_IL1: return pick_pool_specialized<SIG_IL1>(lanes, hint);
-    // SIG_IL1C, SIG_IL2 and SIG_IL4 run the dispatching kernel: its 132 registers keep 3 waves
-    // per SIMD instead of 7 or 8, and fewer resident rays at a time take less time here (160^3 at
-    // 1280 x 720, 16 lanes, dispatching and own kernel, us a call: a guard-less scalar 194 and
-    // 234, two derived sources 218 and 261, four 237 and 269; with 2 lanes 505 and 501)
+    // their own loops keep 7 or 8 waves per SIMD, the dispatching one 3 (160^3 at 1280 x 720, 16
+    // lanes, dispatching and own, us a call: a guard-less scalar 162 and 121, two derived sources
+    // 187 and 141, four 204 and 202; with 2 lanes 475 and 407, 519 and 450, 412 and 374)
+    case SIG_IL1C: return pick_pool_specialized<SIG_IL1C>(lanes, hint);
+    case SIG_IL2: return pick_pool_specialized<SIG_IL2>(lanes, hint);
+    case SIG_IL4: return pick_pool_specialized<SIG_IL4>(lanes, hint);
     default: break;
     }
     switch (lanes) {
