@@ -1427,7 +1427,8 @@ void raycast_kernel(const DevJob* __restrict__ jobs, const float4* __restrict__ 
     if constexpr (kEarly) tab = load_tables(J, tf_pool);
     // tiles cover the box's screen rectangle only (the fill kernel clears the rest)
     int x0, y0, px, py;
-    tile_origin<G>(J, job_tile(tile - J.tile_begin, job, J.tiles_x * J.tiles_y), x0, y0);
+    const int t = tile - J.tile_begin;
+    tile_origin<G>(J, SIGK <= -2 ? job_tile(t, job, J.tiles_x * J.tiles_y) : t, x0, y0);
     const bool in_image = pixel_of<G>(J, x0, y0, (int)threadIdx.x, px, py);
     RaySetup R;
     bool hit;
